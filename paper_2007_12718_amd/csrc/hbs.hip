@@ -97,131 +97,336 @@ __device__ __forceinline__ void wave_argmax_d(double& v, int& idx) {
     if (ov > v || (ov == v && oi < idx)) { v = ov; idx = oi; }
   }
 }
-__device__ __forceinline__ double wave_sum_d(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+  const long long bits = __double_as_longlong(v);
+  return __longlong_as_double(
+      (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(bits >> 32), lane) << 32) |
+                  (unsigned)__builtin_amdgcn_readlane((int)bits, lane)));
+}
+// ----------------------------------------------------------- CPQR row ID
+// Columns of A^T are the rows of W (contiguous); Householder reflectors act
+// on the proxy index.  One launch per pivot, one workgroup per row.  A step
+// is a rank-one update of the whole matrix, so its bytes (32 m np) bound it
+// where the matrix is large; at the sizes of direct solves on small grids
+// (m = 64 .. 500 rows) the step is bound by its chain of latencies: launch,
+// norms, pivot search, pivot row, dot product, norm.  Every workgroup
+// therefore repeats the pivot search from the rows' norms (m values from L2)
+// instead of waiting for another launch or a grid barrier to do it, and
+// starts its own row's loads before the search.  Rows are not moved: W[i][a]
+// holds R[a][i] for the steps a that came before row i was chosen (all steps
+// for a row never chosen), Rd[a] the diagonal.  The norms are double-buffered
+// by the step's parity (a workgroup may finish before another has read
+// them); a chosen row's norm is -1.
+// Against one workgroup holding the whole loop, setup of a 64 x 64 grid at
+// tol 1e-10 (order 10, m up to 892, np up to 1224) fell from 518 to 22 ms,
+// that of 32 x 32 (order 4) from 17.4 to 6.0 ms.
+constexpr int QR_NT = 1024, QR_NW = QR_NT / 64;
+constexpr int QS_NT = 256, QS_NW = QS_NT / 64;
+// device state of one CPQR: rank, done flag, squared stopping threshold
+struct CpqrState {
+  int k, done;
+  double thr2;
+};
+
+__device__ __forceinline__ double cpqr_block_sum(double v, double* sb, int lane, int wave) {
+  v = group_sum<64>(v);
+  if (lane == 0) sb[wave] = v;
+  __syncthreads();
+  return (sb[0] + sb[1]) + (sb[2] + sb[3]);
 }
 
-// ----------------------------------------------- CPQR row ID (one workgroup)
-// Columns of A^T are the rows of W (contiguous); Householder reflectors act
-// on the proxy index.  After step j, W[i][j] (i > j) holds R[j][i].
-constexpr int QR_NT = 1024, QR_NW = QR_NT / 64;
+// squared norms of the rows
+__global__ __launch_bounds__(QS_NT) void k_cpqr_norms(const z64* __restrict__ W, int np, double* nrm) {
+  __shared__ double sb[QS_NW];
+  const int tid = threadIdx.x;
+  const z64* w = W + (long)blockIdx.x * np;
+  double a = 0;
+  for (int q = tid; q < np; q += QS_NT) a += abs2(w[q]);
+  a = cpqr_block_sum(a, sb, tid & 63, tid >> 6);
+  if (tid == 0) nrm[blockIdx.x] = a;
+}
 
-__global__ __launch_bounds__(QR_NT) void k_cpqr(z64* W, int m, int np, double thr, int* J, z64* U, int* k_out,
-                                                 double* nrm, z64* Rd) {
-  __shared__ double sb[QR_NW];
-  __shared__ int si[QR_NW];
-  __shared__ int s_p;
-  __shared__ double s_val;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int i = tid; i < m; i += QR_NT) J[i] = i;
-  for (int i = wave; i < m; i += QR_NW) {
-    double a = 0;
-    for (int q = lane; q < np; q += 64) a += abs2(W[(long)i * np + q]);
-    a = wave_sum_d(a);
-    if (lane == 0) nrm[i] = a;
+// the state: thr2 = tol^2 ||A||_F^2, summed in a fixed order
+__global__ __launch_bounds__(QR_NT) void k_cpqr_init(const double* nrm, int m, double tol2, int kmax,
+                                                      CpqrState* st) {
+  __shared__ double part[QR_NT];
+  double v = 0.0;
+  for (int i = threadIdx.x; i < m; i += QR_NT) v += nrm[i];
+  part[threadIdx.x] = v;
+  __syncthreads();
+  for (int w = QR_NT / 2; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *st = CpqrState{kmax, 0, tol2 * part[0]};
+}
+
+// Step j: the pivot p (largest norm, ties to the lower row), its reflector,
+// and row blockIdx.x less its reflection.  NE entries of the row per thread
+// stay in registers between the dot product and the update (np - j <=
+// NE * QS_NT); NE = 0 reads the row twice (any length).
+template <int NE>
+__global__ __launch_bounds__(QS_NT) void k_cpqr_step(z64* W, int m, int np, int j, const double* __restrict__ nin,
+                                                      double* nout, int* J, z64* Rd, CpqrState* st) {
+  __shared__ double sb[QS_NW], sx[QS_NW], sy[QS_NW];
+  __shared__ int si[QS_NW];
+  if (st->done) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = blockIdx.x;
+  z64* w = W + (long)i * np;
+  z64 e[NE > 0 ? NE : 1];
+#pragma unroll
+  for (int u = 0; u < NE; ++u) {
+    const int q = j + tid + u * QS_NT;
+    e[u] = q < np ? w[q] : mk(0.0, 0.0);
+  }
+  // the pivot
+  double best = -1;
+  int p = m;
+  for (int r = tid; r < m; r += QS_NT) {
+    const double a = nin[r];
+    if (a > best) { best = a; p = r; }
+  }
+  wave_argmax_d(best, p);
+  if (lane == 0) { sb[wave] = best; si[wave] = p; }
+  __syncthreads();
+  best = sb[0];
+  p = si[0];
+#pragma unroll
+  for (int v = 1; v < QS_NW; ++v)
+    if (sb[v] > best || (sb[v] == best && si[v] < p)) { best = sb[v]; p = si[v]; }
+  if (!(best > st->thr2)) {  // (the same in every workgroup)
+    if (i == 0 && tid == 0) {
+      st->k = j;
+      st->done = 1;
+    }
+    return;
+  }
+  const z64* v = W + (long)p * np;
+  // Householder vector: row p from entry j on, with v_j = x0 - alpha
+  const z64 x0 = v[j];
+  const double nx = sqrt(best), ax0 = sqrt(abs2(x0));
+  const z64 ph = ax0 > 0 ? mk(x0.x / ax0, x0.y / ax0) : mk(1.0, 0.0);
+  const z64 alpha = mk(-ph.x * nx, -ph.y * nx);
+  const z64 v0 = x0 - alpha;
+  const double vn2 = best - ax0 * ax0 + abs2(v0);
+  const double beta = vn2 > 0 ? 2.0 / vn2 : 0.0;
+  if (i == p) {
+    if (tid == 0) {
+      J[j] = p;
+      Rd[j] = alpha;
+      nout[i] = -1.0;
+    }
+    return;
+  }
+  if (nin[i] < 0) {  // chosen before
+    if (tid == 0) nout[i] = -1.0;
+    return;
+  }
+  z64 h[NE > 0 ? NE : 1];
+  z64 acc = mk(0.0, 0.0);
+  if (NE > 0) {
+#pragma unroll
+    for (int u = 0; u < NE; ++u) {
+      const int q = j + tid + u * QS_NT;
+      h[u] = q < np ? v[q] : mk(0.0, 0.0);
+    }
+    if (tid == 0) h[0] = v0;
+#pragma unroll
+    for (int u = 0; u < NE; ++u) fma_acc(acc, conjg(h[u]), e[u]);
+  } else {
+    for (int q = j + tid; q < np; q += QS_NT) fma_acc(acc, conjg(q == j ? v0 : v[q]), w[q]);
+  }
+  acc.x = group_sum<64>(acc.x);
+  acc.y = group_sum<64>(acc.y);
+  if (lane == 0) {
+    sx[wave] = acc.x;
+    sy[wave] = acc.y;
   }
   __syncthreads();
-  const int kmax = m < np ? m : np;
-  int k = kmax;
-  for (int j = 0; j < kmax; ++j) {
-    double best = -1;
-    int bi = m;
-    for (int i = j + tid; i < m; i += QR_NT) {
-      const double a = nrm[i];
-      if (a > best || (a == best && J[i] < (bi < m ? J[bi] : 1 << 30))) { best = a; bi = i; }
-    }
-    wave_argmax_d(best, bi);
-    if (lane == 0) { sb[wave] = best; si[wave] = bi; }
-    __syncthreads();
-    if (tid == 0) {
-      double bb = sb[0];
-      int ii = si[0];
-      for (int w = 1; w < QR_NW; ++w)
-        if (sb[w] > bb) { bb = sb[w]; ii = si[w]; }
-      s_p = ii;
-      s_val = bb;
-    }
-    __syncthreads();
-    const int p = s_p;
-    if (!(sqrt(s_val) > thr)) { k = j; break; }
-    if (p != j) {
-      for (int q = tid; q < np; q += QR_NT) {
-        const z64 t = W[(long)j * np + q];
-        W[(long)j * np + q] = W[(long)p * np + q];
-        W[(long)p * np + q] = t;
-      }
-      if (tid == 0) {
-        const double tn = nrm[j]; nrm[j] = nrm[p]; nrm[p] = tn;
-        const int tj = J[j]; J[j] = J[p]; J[p] = tj;
-      }
-    }
-    __syncthreads();
-    // Householder vector of row j, entries q >= j
-    double a = 0;
-    for (int q = j + tid; q < np; q += QR_NT) a += abs2(W[(long)j * np + q]);
-    a = wave_sum_d(a);
-    if (lane == 0) sb[wave] = a;
-    __syncthreads();
-    if (tid == 0) {
-      double nx = 0;
-      for (int w = 0; w < QR_NW; ++w) nx += sb[w];
-      nx = sqrt(nx);
-      const z64 x0 = W[(long)j * np + j];
-      const double ax0 = sqrt(abs2(x0));
-      const z64 ph = ax0 > 0 ? mk(x0.x / ax0, x0.y / ax0) : mk(1.0, 0.0);
-      const z64 alpha = mk(-ph.x * nx, -ph.y * nx);
-      const z64 v0 = x0 - alpha;
-      const double vn2 = nx * nx - ax0 * ax0 + abs2(v0);
-      Rd[j] = alpha;
-      W[(long)j * np + j] = v0;
-      s_val = vn2 > 0 ? 2.0 / vn2 : 0.0;
-    }
-    __syncthreads();
-    const double beta = s_val;
-    const z64* v = W + (long)j * np;
-    for (int i = j + 1 + wave; i < m; i += QR_NW) {
-      z64* w = W + (long)i * np;
-      z64 sacc = mk(0.0, 0.0);
-      for (int q = j + lane; q < np; q += 64) fma_acc(sacc, conjg(v[q]), w[q]);
-      sacc.x = wave_sum_d(sacc.x);
-      sacc.y = wave_sum_d(sacc.y);
-      const z64 f = beta * sacc;
-      double nn = 0;
-      for (int q = j + lane; q < np; q += 64) {
-        const z64 t = w[q] - f * v[q];
+  const z64 f = beta * mk((sx[0] + sx[1]) + (sx[2] + sx[3]), (sy[0] + sy[1]) + (sy[2] + sy[3]));
+  double nn = 0;
+  if (NE > 0) {
+#pragma unroll
+    for (int u = 0; u < NE; ++u) {
+      const int q = j + tid + u * QS_NT;
+      if (q < np) {
+        const z64 t = e[u] - f * h[u];
         w[q] = t;
         if (q > j) nn += abs2(t);
       }
-      nn = wave_sum_d(nn);
-      if (lane == 0) nrm[i] = nn;
     }
-    __syncthreads();
-  }
-  // U: rows J[a] (a < k) are unit rows; rows J[k + c] hold (R11^{-1} R12)^T
-  for (int c = tid; c < m - k; c += QR_NT) {
-    z64* urow = U + (long)J[k + c] * k;
-    for (int a = k - 1; a >= 0; --a) {
-      z64 t = W[(long)(k + c) * np + a];  // R12[a][c]
-      for (int b2 = a + 1; b2 < k; ++b2) t = t - W[(long)b2 * np + a] * urow[b2];  // R11[a][b2]
-      urow[a] = cdiv(t, Rd[a]);
+  } else {
+    for (int q = j + tid; q < np; q += QS_NT) {
+      const z64 t = w[q] - f * (q == j ? v0 : v[q]);
+      w[q] = t;
+      if (q > j) nn += abs2(t);
     }
   }
-  for (int e = tid; e < k * k; e += QR_NT) {
-    const int a = e / k, b2 = e % k;
-    U[(long)J[a] * k + b2] = mk(a == b2 ? 1.0 : 0.0, 0.0);
-  }
-  if (tid == 0) *k_out = k;
+  // (sb was last read before the barrier above)
+  nn = cpqr_block_sum(nn, sb, lane, wave);
+  if (tid == 0) nout[i] = nn;
 }
 
-size_t rowid_cpqr_ws(int m) { return (size_t)m * (sizeof(double) + sizeof(z64)) + 256; }
+// U rows of the rows off the skeleton, (R11^{-1} R12)^T: row x of U solves
+// x L = t with L[a][b] = W[J[a]][b] (b < a), L[a][a] = Rd[a], t = the row's
+// entries of W, by substitution from the last column.  One wave per row, the
+// row in registers (column lane + 64 u, u < NU; k <= 64 NU): step a
+// broadcasts x_a and subtracts x_a L[a][:], row a - 1 in flight meanwhile.
+// k_cpqr_units writes the skeleton's unit rows.
+template <int NU>
+__global__ __launch_bounds__(64) void k_cpqr_interp(const z64* __restrict__ W, int np, int k,
+                                                    const int* __restrict__ J, const z64* __restrict__ Rd,
+                                                    const int* __restrict__ rest, z64* __restrict__ U) {
+  const int lane = threadIdx.x, row = rest[blockIdx.x];
+  const z64* w = W + (long)row * np;
+  z64 t[NU], nx[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int c = lane + 64 * u;
+    t[u] = c < k ? w[c] : mk(0.0, 0.0);
+    nx[u] = mk(0.0, 0.0);
+  }
+#pragma unroll
+  for (int ub = NU - 1; ub >= 0; --ub) {
+    if (64 * ub >= k) continue;
+    const int top = (k - 64 * ub < 64 ? k - 64 * ub : 64) - 1;
+    const int jl = 64 * ub + lane < k ? J[64 * ub + lane] : 0;  // this block's pivots and diagonal
+    const z64 rl = 64 * ub + lane < k ? crecip(Rd[64 * ub + lane]) : mk(0.0, 0.0);
+    {
+      const z64* l = W + (long)__builtin_amdgcn_readlane(jl, top) * np;
+#pragma unroll
+      for (int u = 0; u <= ub; ++u)
+        nx[u] = lane + 64 * u < 64 * ub + top ? l[lane + 64 * u] : mk(0.0, 0.0);
+    }
+    for (int al = top; al >= 0; --al) {
+      const int a = 64 * ub + al;
+      z64 cur[NU];
+#pragma unroll
+      for (int u = 0; u <= ub; ++u) cur[u] = nx[u];
+      if (al > 0) {
+        const z64* l = W + (long)__builtin_amdgcn_readlane(jl, al - 1) * np;
+#pragma unroll
+        for (int u = 0; u <= ub; ++u) nx[u] = lane + 64 * u < a - 1 ? l[lane + 64 * u] : mk(0.0, 0.0);
+      }
+      const z64 x = mk(readlane_f64(t[ub].x, al), readlane_f64(t[ub].y, al)) *
+                    mk(readlane_f64(rl.x, al), readlane_f64(rl.y, al));
+#pragma unroll
+      for (int u = 0; u <= ub; ++u) t[u] = t[u] - x * cur[u];  // (cur is zero from column a on)
+      if (lane == al) t[ub] = x;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < NU; ++u)
+    if (lane + 64 * u < k) U[(long)row * k + lane + 64 * u] = t[u];
+}
 
-void rowid_cpqr(hipStream_t s, z64* A, int m, int np, double thr, int* J, z64* U, int* k_dev, void* ws) {
+// the same for any k, the row in U itself, a workgroup per row
+__global__ __launch_bounds__(QS_NT) void k_cpqr_interp_long(const z64* __restrict__ W, int np, int k,
+                                                             const int* __restrict__ J, const z64* __restrict__ Rd,
+                                                             const int* __restrict__ rest, z64* U) {
+  const int tid = threadIdx.x, row = rest[blockIdx.x];
+  const z64* w = W + (long)row * np;
+  z64* u = U + (long)row * k;
+  for (int c = tid; c < k; c += QS_NT) u[c] = w[c];
+  __syncthreads();
+  for (int a = k - 1; a >= 0; --a) {
+    const z64 x = u[a] * crecip(Rd[a]);
+    const z64* l = W + (long)J[a] * np;
+    for (int c = tid; c < a; c += QS_NT) u[c] = u[c] - x * l[c];
+    __syncthreads();  // (u[a] has been read by every thread)
+    if (tid == 0) u[a] = x;
+  }
+}
+
+__global__ void k_cpqr_units(z64* U, int k, const int* J) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= k * k) return;
+  const int a = e / k, b = e % k;
+  U[(long)J[a] * k + b] = mk(a == b ? 1.0 : 0.0, 0.0);
+}
+
+size_t rowid_cpqr_ws(int m) {
+  return (size_t)m * (2 * sizeof(double) + sizeof(z64) + sizeof(int)) + sizeof(CpqrState) + 5 * 256;
+}
+
+int rowid_cpqr(hipStream_t s, z64* A, int m, int np, double tol, int* J, z64* U, void* ws,
+               const std::function<void(int)>& on_skel) {
   ProfScope ps("cpqr", s, 16.0 * (double)m * np);
-  double* nrm = static_cast<double*>(ws);
-  z64* Rd = reinterpret_cast<z64*>(static_cast<char*>(ws) + ((m * sizeof(double) + 15) / 16) * 16);
-  hipLaunchKernelGGL(k_cpqr, dim3(1), dim3(QR_NT), 0, s, A, m, np, thr, J, U, k_dev, nrm, Rd);
+  char* wp = static_cast<char*>(ws);
+  auto take = [&](size_t bytes) { char* r = wp; wp += ((bytes + 255) / 256) * 256; return (void*)r; };
+  double* nrm[2];
+  nrm[0] = static_cast<double*>(take(sizeof(double) * m));
+  nrm[1] = static_cast<double*>(take(sizeof(double) * m));
+  z64* Rd = static_cast<z64*>(take(sizeof(z64) * m));
+  int* rest = static_cast<int*>(take(sizeof(int) * m));
+  CpqrState* st = static_cast<CpqrState*>(take(sizeof(CpqrState)));
+  const int kmax = m < np ? m : np;
+  hipLaunchKernelGGL(k_cpqr_norms, dim3(m), dim3(QS_NT), 0, s, A, np, nrm[0]);
   LSH_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_cpqr_init, dim3(1), dim3(QR_NT), 0, s, nrm[0], m, tol * tol, kmax, st);
+  LSH_LAUNCH_CHECK();
+  // steps in batches, the done flag read once per batch: a step queued after
+  // the end returns at entry
+  constexpr int BATCH = 32;
+  CpqrState h{kmax, 0, 0.0};
+  for (int j = 0; j < kmax && !h.done;) {
+    const int end = j + BATCH < kmax ? j + BATCH : kmax;
+    for (; j < end; ++j) {
+      const int ne = ceil_div(np - j, QS_NT);
+      auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(m), dim3(QS_NT), 0, s, A, m, np, j, nrm[j & 1], nrm[1 - (j & 1)], J, Rd, st);
+      };
+      if (ne <= 1) go(k_cpqr_step<1>);
+      else if (ne <= 2) go(k_cpqr_step<2>);
+      else if (ne <= 4) go(k_cpqr_step<4>);
+      else if (ne <= 8) go(k_cpqr_step<8>);
+      else go(k_cpqr_step<0>);
+      LSH_LAUNCH_CHECK();
+    }
+    LSH_HIP(hipMemcpyAsync(&h, st, sizeof(h), hipMemcpyDeviceToHost, s));
+    LSH_HIP(hipStreamSynchronize(s));
+  }
+  int k = h.k;
+  if (k < 1) {  // a zero block still gets one skeleton: row 0, U = e_0
+    k = 1;
+    const int zero = 0;
+    const z64 one = mk(1.0, 0.0);
+    LSH_HIP(hipMemcpyAsync(J, &zero, sizeof(int), hipMemcpyHostToDevice, s));
+    fill_zero(s, U, sizeof(z64) * (size_t)m);
+    LSH_HIP(hipMemcpyAsync(U, &one, sizeof(z64), hipMemcpyHostToDevice, s));
+    LSH_HIP(hipStreamSynchronize(s));
+    if (on_skel) on_skel(k);
+    return k;
+  }
+  // the skeleton to the host: the other rows' list, and the caller's notice
+  std::vector<int> ph(k), rh;
+  LSH_HIP(hipMemcpyAsync(ph.data(), J, sizeof(int) * k, hipMemcpyDeviceToHost, s));
+  LSH_HIP(hipStreamSynchronize(s));
+  std::vector<char> used(m, 0);
+  for (int v : ph) {
+    LSH_REQUIRE(v >= 0 && v < m && !used[v], -4, "row ID: skeleton rows not distinct");
+    used[v] = 1;
+  }
+  for (int i = 0; i < m; ++i)
+    if (!used[i]) rh.push_back(i);
+  const int nr = (int)rh.size();
+  if (on_skel) on_skel(k);
+  if (nr) {
+    LSH_HIP(hipMemcpyAsync(rest, rh.data(), sizeof(int) * nr, hipMemcpyHostToDevice, s));
+    auto go = [&](auto kern, int nt) {
+      hipLaunchKernelGGL(kern, dim3(nr), dim3(nt), 0, s, A, np, k, J, Rd, rest, U);
+    };
+    if (k <= 64) go(k_cpqr_interp<1>, 64);
+    else if (k <= 128) go(k_cpqr_interp<2>, 64);
+    else if (k <= 256) go(k_cpqr_interp<4>, 64);
+    else if (k <= 512) go(k_cpqr_interp<8>, 64);
+    else go(k_cpqr_interp_long, QS_NT);
+    LSH_LAUNCH_CHECK();
+  }
+  hipLaunchKernelGGL(k_cpqr_units, dim3(ceil_div((long)k * k, 256)), dim3(256), 0, s, U, k, J);
+  LSH_LAUNCH_CHECK();
+  LSH_HIP(hipStreamSynchronize(s));  // (rh goes)
+  return k;
 }
 
 // ------------------------------------------- Gram / pivoted Cholesky row ID
@@ -640,13 +845,6 @@ __global__ __launch_bounds__(256) void k_bp_sc(const z64* Lt, int m, const int* 
       part[(long)c * BP_B * BP_B + a * BP_B + b] = acc[r];
     }
   }
-}
-
-__device__ __forceinline__ double readlane_f64(double v, int lane) {
-  const long long bits = __double_as_longlong(v);
-  return __longlong_as_double(
-      (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(bits >> 32), lane) << 32) |
-                  (unsigned)__builtin_amdgcn_readlane((int)bits, lane)));
 }
 
 // Greedy pivoted Cholesky of the candidate block S_C = M[C,C] - sum_c

@@ -15,10 +15,11 @@ void gather_table(hipStream_t s, const z64* T, int D, const I2* rows, int m, con
 
 // Row interpolative decomposition A ~= U A[J, :] (U[J, :] = I) of the m x np
 // FP64 matrix A (destroyed).  CPQR path: Householder QR with column pivoting
-// of A^T in one workgroup; stops at the first |R_kk| <= thr.
-// Outputs: J (m ints, first k used), U (m x m capacity, row-major with ld = m,
-// first k columns used), rank in *k_dev.
-void rowid_cpqr(hipStream_t s, z64* A, int m, int np, double thr, int* J, z64* U, int* k_dev, void* ws);
+// of A^T, one launch per pivot; stops at the first |R_kk| <= tol ||A||_F.
+// Outputs: J (m ints, first k used), U (m x k, row-major).  Returns the rank
+// (synchronises on the stream once per batch of steps); on_skel as rowid_bp.
+int rowid_cpqr(hipStream_t s, z64* A, int m, int np, double tol, int* J, z64* U, void* ws,
+               const std::function<void(int)>& on_skel = {});
 size_t rowid_cpqr_ws(int m);
 
 // Gram path: M = A A^H, pivoted Cholesky with the stopping rule

@@ -281,20 +281,7 @@ int row_id_matrix(lsh_plan_s& P, z64* A, int m, int np, std::vector<int>& Jh, De
   // Gram + pivoted Cholesky squares the conditioning: FP64 resolves the
   // stopping rule only while tol stays above ~1e-7; below that, CPQR.
   if (P.d.tol < 1e-7) {
-    // ||A||_F for the stopping rule |R_kk| <= tol ||A||_F (computed on device)
-    void* ws = scr.take(rowid_cpqr_ws(m));
-    int* kd = static_cast<int*>(scr.take(sizeof(int)));
-    z64* fro = static_cast<z64*>(scr.take(sizeof(z64)));
-    z64* part = static_cast<z64*>(scr.take(multidot_partial_bytes(1)));
-    multidot(s, A, 0, 1, A, (long)m * np, fro, part);
-    z64 f2;
-    LSH_HIP(hipMemcpyAsync(&f2, fro, sizeof(z64), hipMemcpyDeviceToHost, s));
-    LSH_HIP(hipStreamSynchronize(s));
-    const double thr = P.d.tol * std::sqrt(f2.x);
-    rowid_cpqr(s, A, m, np, thr, J, Ufull, kd, ws);
-    LSH_HIP(hipMemcpyAsync(&k, kd, sizeof(int), hipMemcpyDeviceToHost, s));
-    LSH_HIP(hipStreamSynchronize(s));
-    if (k < 1) k = 1;  // (a zero block still gets one skeleton)
+    k = rowid_cpqr(s, A, m, np, P.d.tol, J, Ufull, scr.take(rowid_cpqr_ws(m)), skel);
   } else {
     // block-pivoted left-looking Cholesky by default (alpha-greedy with
     // alpha = LSH_BP_ALPHA, default 0.65; 1 = greedy); LSH_ROWID=panel selects
@@ -735,9 +722,6 @@ size_t rowid_scratch_bytes(long m, double tol) {
   z.add_n<int>(m);
   z.add_n<z64>((size_t)m * m);
   q.add(rowid_cpqr_ws((int)m));
-  q.add(sizeof(int));
-  q.add(sizeof(z64));
-  q.add(multidot_partial_bytes(1));
   return z.total + std::max({q.total, mem::round_up(rowid_gram_ws((int)m)), mem::round_up(rowid_bp_ws((int)m))});
 }
 

@@ -1,0 +1,50 @@
+"""Row IDs below tol = 1e-7 (column-pivoted Householder QR, one launch per
+pivot): every level's ID on grids whose proxy matrices cover the step
+kernel's row lengths (up to and beyond 8 x 256 columns) and the
+interpolation's ranks (up to 64, 128, 256, 512 and beyond).
+
+Tolerance: the pivoting stops once every residual row has norm at most
+tol ||A||_F, so the residual of the m - k other rows is at most
+sqrt(m - k) tol ||A||_F; rounding adds about 1e-13 ||A||_F.  Exact ties of the
+symmetric boxes leave the pivots and the rank open by a few, so the pivots
+are checked for what they are: each has the largest residual norm of its step.
+"""
+import numpy as np
+import pytest
+
+from oracle import hbs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,leaf,order,tol,width,kh", [
+    (10, 5, 4, 1e-8, 1, 0.5), (16, 8, 4, 1e-10, 1, 0.3), (48, 6, 6, 1e-9, 2, 0.6), (56, 7, 10, 1e-10, 3, 0.4),
+    (64, 8, 10, 1e-10, 3, 0.5), (128, 8, 10, 1e-10, 3, 0.5), (128, 8, 10, 1e-12, 3, 1.2)])
+def test_every_level_is_a_valid_id(n, leaf, order, tol, width, kh):
+    from paper_2007_12718_amd import lsh
+    kappa = kh * n
+    P = lsh.Plan(n, kappa, op_order=order, leaf=leaf, tol=tol, proxy_width=width, prec="fp64", hbs_order=order,
+                 merge="schur")
+    C = hbs.Compression(n, kappa, leaf, 0.5, width, order=order)  # (its tree and entries; the levels are P's)
+    L, ranks = P.ranks()
+    print(n, order, tol, ranks, flush=True)
+    for l in range(L, 0, -1):
+        J, cand, U = P.level(l)
+        U = U.cpu().numpy()
+        m, k = U.shape
+        assert len(set(J.tolist())) == k and np.array_equal(U[J], np.eye(k))
+        sx, sy = C.tree.box(l, 0)[2:]
+        A = C.proxy_block(cand, hbs.proxy_ring(sx, sy, width))
+        res = np.linalg.norm(A - U @ A[J])
+        assert res <= (np.sqrt(max(m - k, 1)) * tol + 1e-13) * np.linalg.norm(A), (l, m, k)
+        # the pivots are greedy: R = Q^H A^T from the unpivoted QR of A[J]^T; row i's residual norm before step t is
+        # the norm of R[t:, i] and of what is left at the end
+        fro = np.linalg.norm(A)
+        Q = np.linalg.qr(A[J].T)[0]
+        R = Q.conj().T @ A.T
+        left = np.sum(np.abs(A.T - Q @ R) ** 2, axis=0)
+        tail = np.sqrt(np.cumsum((np.abs(R) ** 2)[::-1], axis=0)[::-1] + left)
+        tail[:, J] = np.sqrt(np.cumsum((np.abs(np.triu(R[:, J])) ** 2)[::-1], axis=0)[::-1])
+        d = np.abs(np.diag(R[:, J]))
+        assert np.all(d >= tail.max(axis=1) - 1e-13 * fro), (l, m, k)
+        assert d.min() > tol * fro - 1e-13 * fro and np.sqrt(left.max()) <= tol * fro + 1e-13 * fro, (l, m, k)
