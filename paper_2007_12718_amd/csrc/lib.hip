@@ -31,10 +31,12 @@ static int g_apply_fused_min = kApplyFusedMin;
 
 #include "../../include/lsh.h"
 #include "blas.hpp"
+#include "hankel.hpp"
 #include "hbs.hpp"
 #include "ops.hpp"
 #include "plancache.hpp"
 #include "prof.hpp"
+#include "wave.hpp"
 #include "weights.hpp"
 
 namespace lsh {
@@ -116,6 +118,17 @@ struct lsh_plan_s {
   int ng_level = -1;    // the level whose Gram ng holds (-1: none)
   std::vector<I2> ng_prox;  // (host source of its proxy upload)
   ConvOperator op;
+  // The row-ID temporaries (sid) are free once the plan is built; the receiver
+  // sums use them for partial results.  A call waits on the stream for the
+  // previous call's event, so calls on different streams take turns there;
+  // the plan's end waits for the last one.
+  hipEvent_t pts_ev = nullptr;
+  ~lsh_plan_s() {
+    if (pts_ev) {
+      (void)hipEventSynchronize(pts_ev);
+      (void)hipEventDestroy(pts_ev);
+    }
+  }
   std::vector<StencilEntry> st4;
   double tau0_re = 0, tau0_im = 0;
   template <typename R>
@@ -2065,62 +2078,117 @@ void fgmres_multi(lsh_factor_s& F, SolveWs& W, const z64* f, z64* x, int nr, con
   }
 }
 
-// receivers: u(x_r) = h^2 sum_j (i/4) H0(kappa |x_r - x_j|) sigma_j
-constexpr int EV_MAXRHS = 16;
-__global__ __launch_bounds__(256) void k_eval_points(const z64* __restrict__ sig, int n, double h, double gx0,
-                                                     double gy0, double kappa, const double* __restrict__ xy,
-                                                     z64* out, int npts, int nrhs) {
-  __shared__ z64 red[EV_MAXRHS][4];
-  const int pt = blockIdx.x;
-  const double px = xy[2 * pt], py = xy[2 * pt + 1];
-  z64 acc[EV_MAXRHS];
-  for (int r = 0; r < EV_MAXRHS; ++r) acc[r] = mk(0.0, 0.0);
-  const long N = (long)n * n;
-  for (long j = threadIdx.x; j < N; j += blockDim.x) {
-    const int i1 = (int)(j % n), i2 = (int)(j / n);
-    const double dx = px - (gx0 + (i1 + 0.5) * h), dy = py - (gy0 + (i2 + 0.5) * h);
-    const double rr = kappa * sqrt(dx * dx + dy * dy);
-    const z64 g = mk(-0.25 * y0(rr), 0.25 * j0(rr));
-    for (int r = 0; r < EV_MAXRHS; ++r)
-      if (r < nrhs) fma_acc(acc[r], g, sig[r * N + j]);
+// Receivers: u(x_r) = h^2 sum_j (i/4) H0(kappa |x_r - x_j|) sigma_j, and the
+// adjoint.  Bound by the FP64 arithmetic of the kernel values (about 110
+// instructions a pair, green_h0), which are formed once per pair and used for
+// NR right-hand sides.
+constexpr int EV_NT = 256, EV_MAXRHS = 8;
+
+// Sums over one part of the grid for PT points (blockIdx.x) and NR fields:
+// a workgroup takes the nodes [blockIdx.y * chunk, ...), so that a few
+// receivers still fill the chip; PT points share each node's fields.  The
+// sums go to part[part][pt][r], or to out where one part is the whole grid.  One workgroup per receiver over the whole
+// grid with the library's j0 and y0 took 1.74 ms for 64 receivers and 8
+// fields on 512 x 512; this takes 0.165 ms.
+template <int NR, int PT>
+__global__ __launch_bounds__(EV_NT) void k_eval_points(const z64* __restrict__ sig, int n, double h, double gx0,
+                                                       double gy0, double kappa, const double* __restrict__ xy,
+                                                       z64* __restrict__ part, z64* __restrict__ out, int npts,
+                                                       int nrhs, int chunk) {
+  __shared__ z64 red[EV_NT / 64][PT * NR];
+  const int N = n * n, p0 = blockIdx.x * PT, tid = threadIdx.x;
+  double px[PT], py[PT];
+  z64 acc[PT][NR];
+#pragma unroll
+  for (int p = 0; p < PT; ++p) {
+    const int pt = p0 + p < npts ? p0 + p : npts - 1;
+    px[p] = xy[2 * pt];
+    py[p] = xy[2 * pt + 1];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) acc[p][r] = mk(0.0, 0.0);
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int r = 0; r < EV_MAXRHS; ++r) {
-    if (r >= nrhs) break;
-    z64 a = acc[r];
-    for (int off = 32; off > 0; off >>= 1) {
-      a.x += __shfl_xor(a.x, off);
-      a.y += __shfl_xor(a.y, off);
+  const int j0 = blockIdx.y * chunk, j1 = j0 + chunk < N ? j0 + chunk : N;
+  for (int j = j0 + tid; j < j1; j += EV_NT) {
+    const int i2 = j / n, i1 = j - i2 * n;
+    z64 sv[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) sv[r] = sig[(long)(r < nrhs ? r : 0) * N + j];  // (past nrhs: not stored)
+    const double gx = gx0 + (i1 + 0.5) * h, gy = gy0 + (i2 + 0.5) * h;
+#pragma unroll
+    for (int p = 0; p < PT; ++p) {
+      const double dx = px[p] - gx, dy = py[p] - gy;
+      const z64 g = green_h0(kappa * sqrt(dx * dx + dy * dy));
+#pragma unroll
+      for (int r = 0; r < NR; ++r) fma_acc(acc[p][r], g, sv[r]);
     }
-    if (lane == 0) red[r][wave] = a;
   }
+#pragma unroll
+  for (int p = 0; p < PT; ++p)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const z64 a = mk(group_sum<64>(acc[p][r].x), group_sum<64>(acc[p][r].y));
+      if ((tid & 63) == 0) red[tid >> 6][p * NR + r] = a;
+    }
   __syncthreads();
-  if (threadIdx.x < nrhs) {
-    const int r = threadIdx.x;
-    z64 a = red[r][0] + red[r][1] + red[r][2] + red[r][3];
-    out[(long)r * npts + pt] = (h * h) * a;
+  if (tid < PT * NR) {
+    const int pt = p0 + tid / NR, r = tid % NR;
+    const z64 v = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+    if (pt < npts && r < nrhs) {
+      if (out) out[(long)r * npts + pt] = (h * h) * v;
+      else part[((long)blockIdx.y * npts + pt) * nrhs + r] = v;
+    }
   }
 }
 
-// out[m][j] = h^2 sum_r conj(G(|x_r - x_j|)) g[m][r]  (adjoint of the receiver map)
-__global__ __launch_bounds__(256) void k_eval_points_adj(const z64* __restrict__ g, int npts, int nrhs, int n,
-                                                         double h, double gx0, double gy0, double kappa,
-                                                         const double* __restrict__ xy, z64* out) {
-  const long N = (long)n * n;
-  const long j = blockIdx.x * (long)blockDim.x + threadIdx.x;
-  if (j >= N) return;
-  const int i1 = (int)(j % n), i2 = (int)(j / n);
+// out[r][pt] = h^2 sum over the parts, one wave per value, in a fixed order
+__global__ __launch_bounds__(256) void k_points_reduce(const z64* __restrict__ part, int parts, int npts, int nrhs,
+                                                       double h2, z64* out) {
+  const int e = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (e >= npts * nrhs) return;
+  z64 a = mk(0.0, 0.0);
+  for (int q = lane; q < parts; q += 64) a = a + part[(long)q * npts * nrhs + e];
+  a = mk(group_sum<64>(a.x), group_sum<64>(a.y));
+  if (lane == 0) out[(long)(e % nrhs) * npts + e / nrhs] = h2 * a;
+}
+
+// out[m][j] = h^2 sum_r conj(G(|x_r - x_j|)) g[m][r]  (adjoint of the receiver
+// map): a node per thread, the receivers over PG groups of threads (PG > 1
+// where the nodes alone would leave units idle), each group's sums joined in
+// LDS.  64 receivers, 8 fields, 512 x 512: 1.74 -> 0.154 ms.
+template <int NR, int PG>
+__global__ __launch_bounds__(EV_NT) void k_eval_points_adj(const z64* __restrict__ g, int npts, int nrhs, int n,
+                                                           double h, double gx0, double gy0, double kappa,
+                                                           const double* __restrict__ xy, z64* out) {
+  constexpr int JB = EV_NT / PG;
+  __shared__ z64 red[PG > 1 ? PG - 1 : 1][PG > 1 ? NR : 1][PG > 1 ? JB : 1];
+  const int N = n * n, jb = threadIdx.x % JB, pg = threadIdx.x / JB;
+  const int j = blockIdx.x * JB + jb;
+  const int i2 = j / n, i1 = j - i2 * n;
   const double px = gx0 + (i1 + 0.5) * h, py = gy0 + (i2 + 0.5) * h;
-  z64 acc[EV_MAXRHS];
-  for (int m = 0; m < EV_MAXRHS; ++m) acc[m] = mk(0.0, 0.0);
-  for (int r = 0; r < npts; ++r) {
+  z64 acc[NR];
+#pragma unroll
+  for (int m = 0; m < NR; ++m) acc[m] = mk(0.0, 0.0);
+  for (int r = pg; r < npts; r += PG) {
     const double dx = xy[2 * r] - px, dy = xy[2 * r + 1] - py;
-    const double rr = kappa * sqrt(dx * dx + dy * dy);
-    const z64 gc = mk(-0.25 * y0(rr), -0.25 * j0(rr));  // conj((i/4) H0)
-    for (int m = 0; m < EV_MAXRHS; ++m)
-      if (m < nrhs) fma_acc(acc[m], gc, g[(long)m * npts + r]);
+    const z64 gc = conjg(green_h0(kappa * sqrt(dx * dx + dy * dy)));
+#pragma unroll
+    for (int m = 0; m < NR; ++m) fma_acc(acc[m], gc, g[(long)(m < nrhs ? m : 0) * npts + r]);  // (as above)
   }
-  for (int m = 0; m < nrhs; ++m) out[m * N + j] = (h * h) * acc[m];
+  if (PG > 1) {
+    if (pg > 0)
+#pragma unroll
+      for (int m = 0; m < NR; ++m) red[pg - 1][m][jb] = acc[m];
+    __syncthreads();
+    if (pg > 0) return;
+#pragma unroll
+    for (int q = 0; q < PG - 1; ++q)
+#pragma unroll
+      for (int m = 0; m < NR; ++m) acc[m] = acc[m] + red[q][m][jb];
+  }
+  if (j < N)
+#pragma unroll
+    for (int m = 0; m < NR; ++m)
+      if (m < nrhs) out[(long)m * N + j] = (h * h) * acc[m];
 }
 
 // grad[k] = -kappa^2 Re sum_m conj(lambda[m][k]) (u_inc[m][k] + u[m][k])
@@ -2301,9 +2369,22 @@ int lsh_eval_points_adjoint(lsh_plan_t P, const void* g_pts, const double* xy, i
   const long N = (long)P->n * P->n;
   for (int r0 = 0; r0 < nrhs; r0 += EV_MAXRHS) {
     const int nr = nrhs - r0 < EV_MAXRHS ? nrhs - r0 : EV_MAXRHS;
-    hipLaunchKernelGGL(k_eval_points_adj, dim3(ceil_div(N, 256)), dim3(256), 0, s,
-                       static_cast<const z64*>(g_pts) + (long)r0 * npts, npts, nr, P->n, P->h, P->d.x0, P->d.y0,
-                       P->kappa, xy, static_cast<z64*>(out) + r0 * N);
+    const z64* g = static_cast<const z64*>(g_pts) + (long)r0 * npts;
+    z64* o = static_cast<z64*>(out) + r0 * N;
+    // up to 2^17 nodes (eight waves a compute unit) four groups of threads share the receivers
+    const bool split = N <= (1 << 17);
+    auto go = [&](auto k1, auto k4) {
+      if (split)
+        hipLaunchKernelGGL(k4, dim3(ceil_div(N, EV_NT / 4)), dim3(EV_NT), 0, s, g, npts, nr, P->n, P->h, P->d.x0,
+                           P->d.y0, P->kappa, xy, o);
+      else
+        hipLaunchKernelGGL(k1, dim3(ceil_div(N, EV_NT)), dim3(EV_NT), 0, s, g, npts, nr, P->n, P->h, P->d.x0,
+                           P->d.y0, P->kappa, xy, o);
+    };
+    if (nr == 1) go(k_eval_points_adj<1, 1>, k_eval_points_adj<1, 4>);
+    else if (nr == 2) go(k_eval_points_adj<2, 1>, k_eval_points_adj<2, 4>);
+    else if (nr <= 4) go(k_eval_points_adj<4, 1>, k_eval_points_adj<4, 4>);
+    else go(k_eval_points_adj<8, 1>, k_eval_points_adj<8, 4>);
     LSH_LAUNCH_CHECK();
   }
   return LSH_OK;
@@ -3528,13 +3609,48 @@ int lsh_eval_points(lsh_plan_t P, const void* sigma, const double* xy, int npts,
   API_BEGIN
   LSH_REQUIRE(P && sigma && xy && u_pts && npts >= 1 && nrhs >= 1, LSH_ERR_INVALID_ARG, "bad argument");
   hipStream_t s = (hipStream_t)stream;
+  const long N = (long)P->n * P->n;
+  // partial sums in the plan's idle row-ID memory (not under capture, where
+  // the turns between calls could not be ordered)
+  z64* scratch = nullptr;
+  auto turn = [&] {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return false;
+    }
+    if (!P->pts_ev) LSH_HIP(hipEventCreateWithFlags(&P->pts_ev, hipEventDisableTiming));
+    else LSH_HIP(hipStreamWaitEvent(s, P->pts_ev, 0));
+    scratch = reinterpret_cast<z64*>(P->sid.base());
+    return true;
+  };
   for (int r0 = 0; r0 < nrhs; r0 += EV_MAXRHS) {
     const int nr = nrhs - r0 < EV_MAXRHS ? nrhs - r0 : EV_MAXRHS;
-    const long N = (long)P->n * P->n;
-    hipLaunchKernelGGL(k_eval_points, dim3(npts), dim3(256), 0, s, static_cast<const z64*>(sigma) + r0 * N, P->n,
-                       P->h, P->d.x0, P->d.y0, P->kappa, xy, static_cast<z64*>(u_pts) + (long)r0 * npts, npts, nr);
-    LSH_LAUNCH_CHECK();
+    const z64* sg = static_cast<const z64*>(sigma) + r0 * N;
+    z64* o = static_cast<z64*>(u_pts) + (long)r0 * npts;
+    auto go = [&](auto kern, int pt) {
+      // about eight workgroups a compute unit, each thread at least four nodes, within the scratch
+      const int groups = ceil_div(npts, pt);
+      const size_t each = sizeof(z64) * (size_t)npts * nr;
+      long parts = std::min<long>({2048 / groups, N / (4 * EV_NT), (long)(P->sid.cap() / each)});
+      if (parts > 1 && !scratch && !turn()) parts = 1;
+      const int chunk = ceil_div(ceil_div(N, std::max(1L, parts)), EV_NT) * EV_NT;
+      parts = ceil_div(N, chunk);
+      z64* direct = parts > 1 ? nullptr : o;
+      hipLaunchKernelGGL(kern, dim3(groups, parts), dim3(EV_NT), 0, s, sg, P->n, P->h, P->d.x0, P->d.y0, P->kappa,
+                         xy, scratch, direct, npts, nr, chunk);
+      LSH_LAUNCH_CHECK();
+      if (direct) return;
+      hipLaunchKernelGGL(k_points_reduce, dim3(ceil_div((long)npts * nr, 4)), dim3(256), 0, s, scratch, (int)parts,
+                         npts, nr, P->h * P->h, o);
+      LSH_LAUNCH_CHECK();
+    };
+    if (nr == 1) go(k_eval_points<1, 4>, 4);
+    else if (nr == 2) go(k_eval_points<2, 4>, 4);
+    else if (nr <= 4) go(k_eval_points<4, 2>, 2);
+    else go(k_eval_points<8, 2>, 2);
   }
+  if (scratch) LSH_HIP(hipEventRecord(P->pts_ev, s));
   return LSH_OK;
   API_END
 }
