@@ -5,28 +5,16 @@
 
 namespace lsh {
 
-// Power-of-two FP64 FFT of rows held in LDS (length <= 4096).
-struct FFTPlan {
-  int M = 0, logM = 0;
-  DevBuf tw;  // exp(-2 pi i k / M), k < M
-  void init(int M_, hipStream_t s);
-};
-
-// Batched row transforms: out[r][k] (k < nout) = DFT_M(in[r][0 .. nin)) (zero padded).
-// inverse: conjugate twiddles, no scaling.
-void fft_rows(hipStream_t s, const FFTPlan& P, const z64* in, long ldin, int nin, z64* out, long ldout,
-              int nout, int nrows, bool inverse);
-// out[c][r] = in[r][c]
-void transpose_z(hipStream_t s, const z64* in, long ldin, z64* out, long ldout, int rows, int cols);
-
 // y = x + kappa^2 b (K * x) (and the plain convolution u = K * x) with the
-// zero-padded circulant embedding of size M x M, M = 2^k >= 2n.
+// zero-padded circulant embedding of size M x M, M >= 2n a power of two or
+// three or five times one.
 struct ConvOperator {
   int n = 0, M = 0;
   double kappa = 0;
-  FFTPlan fft;
+  int group = 1;    // vectors per launch
+  DevBuf tw;        // exp(-2 pi i k / M), k < M
   DevBuf khat;      // spectrum of the kernel scaled by 1/M^2, rows and columns 0 .. M/2 (even in both)
-  DevBuf w1, w2;    // n x M and M x n work arrays
+  DevBuf w1, w2;    // M x n and n x M work arrays of a group
   // (device memory from the bound arena; scr: staging of the stencil)
   void init(hipStream_t s, int n_, double h, double kappa_, const z64* table, int D,
             const std::vector<StencilEntry>& stencil, mem::Arena& scr);
