@@ -98,17 +98,18 @@ int lsh_gemm_force_variant(int variant);
  * default. */
 int lsh_fused_levels(int min_boxes);
 
-/* Preconditioner apply (Algorithm 2, M = A^-1 approximately): a Woodbury
- * level whose box vectors (boxes times right-hand sides) number at least
- * min_vectors, and whose per-box vectors fit one workgroup's LDS, runs each
- * pass in one launch with a workgroup per box vector and its intermediates in
- * LDS; the other levels run the step's six to seven batched products.  The
- * two forms agree to rounding (different summation orders).  Affects later
- * applies of M (lsh_apply_precond with transpose = 0, and the
- * preconditioner inside lsh_solve); M^T (lsh_apply_precond with transpose = 1,
- * lsh_solve_adjoint) keeps the batched products.  Process-wide setting, not
- * thread-safe against concurrent applies: 0 never fuses, 1 fuses every such
- * level, -1 restores the default (128).  Returns LSH_ERR_INVALID_ARG below -1. */
+/* Preconditioner apply (Algorithm 2, M = A^-1 approximately, and its
+ * transpose): a Woodbury level whose per-box vectors fit one workgroup's LDS
+ * can run each pass in one launch with a workgroup per box and group of
+ * right-hand sides and its intermediates in LDS; the other levels run the
+ * step's six to seven batched products.  The two forms agree to rounding
+ * (different summation orders).  Affects later applies (lsh_apply_precond and
+ * the preconditioners inside lsh_solve and lsh_solve_adjoint).  Process-wide
+ * setting, not thread-safe against concurrent applies: 0 never fuses, 1 fuses
+ * every such level, a larger number those with at least min_vectors box
+ * vectors (boxes times right-hand sides), -1 restores the default, a rule on
+ * the level's size and its number of box vectors.  Returns
+ * LSH_ERR_INVALID_ARG below -1. */
 int lsh_apply_fused_levels(int min_vectors);
 
 #ifdef __cplusplus

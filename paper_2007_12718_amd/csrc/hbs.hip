@@ -1,6 +1,7 @@
 // HBS compression (paper Sec. 3.2), leaf factor (Alg. 1, leaf loop) and the
 // leaf steps of the apply (Alg. 2) on gfx950.
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 
@@ -1760,172 +1761,325 @@ void leaf_tdown(hipStream_t s, const cplx<R>* XT, const cplx<R>* UL, int mL, int
 }
 
 // ------------------------------------------- apply, one Woodbury level fused
-// Rows of one box product inside a workgroup of NT threads: out(i, sum_j
-// A_i[j] x_i[j]) for i < M, j < N, with x_i in LDS.  16 lanes per row (lane s
-// takes columns s + 16u of each 64-column chunk), P rows per 16-lane group at
-// a time with every load issued before the products; column u of a chunk goes
-// to partial sum u, then (s0 + s1) + (s2 + s3) and a DPP butterfly over the
-// 16 lanes.  (The same arithmetic for any NT.)
-template <typename R, int P, int NT, typename RowA, typename RowX, typename Out>
-__device__ __forceinline__ void box_rows(int M, int N, RowA rowA, RowX rowX, Out out) {
-  constexpr int NG = NT / 16;
-  const int sub = threadIdx.x & 15, grp = threadIdx.x >> 4;
-  for (int i0 = grp * P; i0 < M; i0 += NG * P) {
-    cplx<R> acc[P][4];
+// One product of a box inside a workgroup of NT threads: H blocks (1 or 2) of M
+// rows of N entries (row-major, packed; the second block sh entries after the
+// first) times the vectors x_h of NV right-hand sides in LDS.  L lanes per row,
+// 4, 8 or 16 by the row length (the short rows of deep levels would leave most
+// of 16 lanes idle, and the instructions, not the bytes, bound such a level):
+// lane s takes columns s + L u of each 4 L-column chunk, P rows per lane group
+// at a time, the products of a row added column by column in each lane and
+// then over the lanes by DPP (the same arithmetic for any NT and NV).
+template <typename R>
+struct BoxProd {
+  const cplx<R>* A;
+  int M, N, H, sh, lg;  // lg: log2 L
+  __device__ __forceinline__ BoxProd(const cplx<R>* A_, int M_, int N_, int H_, int sh_)
+      : A(A_), M(M_), N(N_), H(H_), sh(sh_), lg(N_ <= 16 ? 2 : N_ <= 32 ? 3 : 4) {}
+};
+template <typename R, int P>
+struct BoxFrag {
+  cplx<R> a[P][4];
+};
+
+// entries of chunk j0 of row block blk; outside the product those of its last
+// row block, row or column instead (their sums are not stored, their x is zero)
+template <typename R, int P>
+__device__ __forceinline__ void box_load(BoxFrag<R, P>& f, const BoxProd<R>& m, int blk, int j0) {
+  const int L = 1 << m.lg, sub = threadIdx.x & (L - 1), nbk = (m.M + P - 1) / P, last = m.H * nbk - 1;
+  blk = blk < last ? blk : last;
+  const bool h1 = blk >= nbk;
+  const int i0 = (blk - (h1 ? nbk : 0)) * P;
+  const char* base = reinterpret_cast<const char*>(m.A);
+  unsigned row[P], col[4];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const int i = i0 + p < m.M ? i0 + p : m.M - 1;
+    row[p] = (unsigned)((h1 ? m.sh : 0) + i * m.N) * (unsigned)sizeof(cplx<R>);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int j = j0 + sub + (u << m.lg);
+    col[u] = (unsigned)(j < m.N ? j : m.N - 1) * (unsigned)sizeof(cplx<R>);
+  }
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f.a[p][u] = *reinterpret_cast<const cplx<R>*>(base + (row[p] + col[u]));
+}
+template <typename R, int P>
+__device__ __forceinline__ void box_first(BoxFrag<R, P>& f, const BoxProd<R>& m) {
+  box_load<R, P>(f, m, threadIdx.x >> m.lg, 0);
+}
+
+// out(h, i, v, sum) for every row and vector; f: this group's first chunk,
+// already loaded.  The next chunk (or row block) is in flight during the
+// products of the current one.
+template <typename R, int P, int NT, int NV, typename Out>
+__device__ __forceinline__ void box_run(const BoxProd<R>& m, BoxFrag<R, P>& f, const cplx<R>* x0, const cplx<R>* x1,
+                                        int ldx, Out out) {
+  const int L = 1 << m.lg, NG = NT >> m.lg, sub = threadIdx.x & (L - 1), grp = threadIdx.x >> m.lg;
+  const int nbk = (m.M + P - 1) / P, nblk = m.H * nbk;
+  for (int blk = grp; blk < nblk; blk += NG) {
+    const bool h1 = blk >= nbk;
+    const int i0 = (blk - (h1 ? nbk : 0)) * P;
+    const cplx<R>* x = h1 ? x1 : x0;
+    cplx<R> acc[P][NV];
 #pragma unroll
     for (int p = 0; p < P; ++p)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) acc[p][u] = mk<R>(0, 0);
-    for (int j0 = 0; j0 < N; j0 += 64) {
-      cplx<R> a[P][4], x[P][4];
+      for (int v = 0; v < NV; ++v) acc[p][v] = mk<R>(0, 0);
+    for (int j0 = 0; j0 < m.N; j0 += 4 * L) {
+      BoxFrag<R, P> nx;
+      const bool more = j0 + 4 * L < m.N;
+      if (more || blk + NG < nblk) box_load<R, P>(nx, m, more ? blk : blk + NG, more ? j0 + 4 * L : 0);
 #pragma unroll
-      for (int p = 0; p < P; ++p) {
-        const int i = i0 + p < M ? i0 + p : M - 1;
-        const cplx<R>* ar = rowA(i);
-        const cplx<R>* xr = rowX(i);
+      for (int u = 0; u < 4; ++u) {
+        const int j = j0 + sub + (u << m.lg);
+        cplx<R> xv[NV];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int jj = j0 + sub + 16 * u;
-          const bool ok = i0 + p < M && jj < N;
-          a[p][u] = ok ? ar[jj] : mk<R>(0, 0);
-          x[p][u] = ok ? xr[jj] : mk<R>(0, 0);
+        for (int v = 0; v < NV; ++v) {
+          const cplx<R> t = x[v * ldx + (j < m.N ? j : m.N - 1)];
+          xv[v] = mk(j < m.N ? t.x : R(0), j < m.N ? t.y : R(0));
         }
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+          for (int v = 0; v < NV; ++v) fma_acc(acc[p][v], f.a[p][u], xv[v]);
       }
-#pragma unroll
-      for (int p = 0; p < P; ++p)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) fma_acc(acc[p][u], a[p][u], x[p][u]);
+      f = nx;
     }
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-      cplx<R> t = (acc[p][0] + acc[p][1]) + (acc[p][2] + acc[p][3]);
-      t.x = group_sum<16>(t.x);
-      t.y = group_sum<16>(t.y);
-      if (sub == 0 && i0 + p < M) out(i0 + p, t);
-    }
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        cplx<R> t = mk(group_sum<4>(acc[p][v].x), group_sum<4>(acc[p][v].y));
+        if (m.lg >= 3) t = t + mk(dpp_mov<0x141>(t.x), dpp_mov<0x141>(t.y));  // row_half_mirror
+        if (m.lg >= 4) t = t + mk(dpp_mov<0x140>(t.x), dpp_mov<0x140>(t.y));  // row_mirror
+        if (sub == 0 && i0 + p < m.M) out(h1 ? 1 : 0, i0 + p, v, t);
+      }
   }
 }
 
-// Up, one level (Algorithm 2's upward step on a Woodbury level): per box
-// vector v (box v mod nb) with input [rt_a; rt_b] (2c),
-//   q = [L^T rt_a; R^T rt_b], y = W'_b q, t = in - [S_a L y1; S_b R y2],
-//   out_v = U_l^T t (k),
-// every intermediate in LDS: one workgroup of NT threads per box vector.
-template <typename R, int NT>
-__global__ __launch_bounds__(NT) void k_level_up(LevelApply<R> A, const cplx<R>* __restrict__ in,
-                                                 cplx<R>* __restrict__ out) {
-  extern __shared__ __align__(16) unsigned char lvl_lds[];
-  const int c = A.c, k = A.k, r = A.r;
-  const long v = blockIdx.x;
-  const long b = v % A.nb;
-  cplx<R>* xs = reinterpret_cast<cplx<R>*>(lvl_lds);  // [2c]
-  cplx<R>* q = xs + 2 * c;                             // [2r]
-  cplx<R>* y = q + 2 * r;                              // [2r]
-  cplx<R>* t = y + 2 * r;                              // [2c]
-  const cplx<R>* iv = in + v * 2 * c;
-  for (int i = threadIdx.x; i < 2 * c; i += NT) xs[i] = iv[i];
-  __syncthreads();
-  box_rows<R, 2, NT>(2 * r, c, [&](int i) { return A.Q + (long)i * c; },
-                     [&](int i) { return i < r ? xs : xs + c; }, [&](int i, cplx<R> s) { q[i] = s; });
-  __syncthreads();
-  const cplx<R>* Wb = A.Ci + b * 4 * r * r;
-  box_rows<R, 2, NT>(2 * r, 2 * r, [&](int i) { return Wb + (long)i * 2 * r; },
-                     [&](int) { return (const cplx<R>*)q; }, [&](int i, cplx<R> s) { y[i] = s; });
-  __syncthreads();
-  const cplx<R>* Pb = A.Pa + b * 2 * c * r;  // [S_a L; S_b R] of the two children, rows contiguous
-  box_rows<R, 2, NT>(2 * c, r, [&](int i) { return Pb + (long)i * r; }, [&](int i) { return i < c ? y : y + r; },
-                     [&](int i, cplx<R> s) { t[i] = xs[i] - s; });
-  __syncthreads();
-  cplx<R>* ov = out + v * k;
-  box_rows<R, 2, NT>(k, 2 * c, [&](int i) { return A.Ut + (long)i * 2 * c; },
-                     [&](int) { return (const cplx<R>*)t; }, [&](int i, cplx<R> s) { ov[i] = s; });
-}
-
-// Down, one level: per box vector v with wt_v (k) and the children's rt (2c),
-//   u = U_l wt_v, d = rt - diag(S_a, S_b) u, o = X_tau d (the Woodbury form
-//   as above), wt_children = [G_ab o_b; G_ba o_a] + u,
-// every intermediate in LDS.
-template <typename R, int NT>
-__global__ __launch_bounds__(NT) void k_level_down(LevelApply<R> A, const cplx<R>* __restrict__ wt,
-                                                   const cplx<R>* __restrict__ rtc, cplx<R>* __restrict__ wc) {
-  extern __shared__ __align__(16) unsigned char lvl_lds[];
-  const int c = A.c, k = A.k, r = A.r;
-  const long v = blockIdx.x;
-  const long b = v % A.nb;
-  cplx<R>* w = reinterpret_cast<cplx<R>*>(lvl_lds);  // [k]
-  cplx<R>* u = w + k;                                 // [2c]
-  cplx<R>* d = u + 2 * c;                             // [2c]
-  cplx<R>* q = d + 2 * c;                             // [2r]
-  cplx<R>* y = q + 2 * r;                             // [2r]
-  cplx<R>* o = y + 2 * r;                             // [2c]
-  const cplx<R>* wv = wt + v * k;
-  for (int i = threadIdx.x; i < k; i += NT) w[i] = wv[i];
-  __syncthreads();
-  box_rows<R, 2, NT>(2 * c, k, [&](int i) { return A.U + (long)i * k; }, [&](int) { return (const cplx<R>*)w; },
-                     [&](int i, cplx<R> s) { u[i] = s; });
-  __syncthreads();
-  const cplx<R>* Sb = A.S + b * 2 * c * c;  // S_a, S_b of the two children, rows contiguous
-  const cplx<R>* rv = rtc + v * 2 * c;
-  box_rows<R, 2, NT>(2 * c, c, [&](int i) { return Sb + (long)i * c; }, [&](int i) { return i < c ? u : u + c; },
-                     [&](int i, cplx<R> s) { d[i] = rv[i] - s; });
-  __syncthreads();
-  box_rows<R, 2, NT>(2 * r, c, [&](int i) { return A.Q + (long)i * c; }, [&](int i) { return i < r ? d : d + c; },
-                     [&](int i, cplx<R> s) { q[i] = s; });
-  __syncthreads();
-  const cplx<R>* Wb = A.Ci + b * 4 * r * r;
-  box_rows<R, 2, NT>(2 * r, 2 * r, [&](int i) { return Wb + (long)i * 2 * r; },
-                     [&](int) { return (const cplx<R>*)q; }, [&](int i, cplx<R> s) { y[i] = s; });
-  __syncthreads();
-  const cplx<R>* Pb = A.Pa + b * 2 * c * r;
-  box_rows<R, 2, NT>(2 * c, r, [&](int i) { return Pb + (long)i * r; }, [&](int i) { return i < c ? y : y + r; },
-                     [&](int i, cplx<R> s) { o[i] = d[i] - s; });
-  __syncthreads();
-  cplx<R>* ov = wc + v * 2 * c;
-  box_rows<R, 2, NT>(2 * c, c, [&](int i) { return i < c ? A.Gab + (long)i * c : A.Gba + (long)(i - c) * c; },
-                     [&](int i) { return i < c ? o + c : o; }, [&](int i, cplx<R> s) { ov[i] = s + u[i]; });
-}
-
-// threads per box vector: about 8192 waves in all (few vectors: more lanes on
-// each vector's rows)
-static int level_threads(int nvec) { return nvec <= 512 ? 1024 : nvec <= 1024 ? 512 : 256; }
-
+// A level's step in one launch: a workgroup per box and group of NV right-hand
+// sides, which reads the box's matrices once for the group, every
+// intermediate vector in LDS.  Between the four to six products stand
+// barriers; each product's first entries are loaded two products ahead, so
+// that a deep level (c = 29, 8192 boxes), whose products are one or two such
+// loads, waits for memory once and not six times.  Box vector (right-hand
+// side q, box b) is number q nb + b.
+// The box matrices come at 2.7 to 3.1 TB/s (1024 x 1024, FP32, one vector:
+// the down pass of 8192 boxes of c = 28, 184 MB, 68 us, of 256 of c = 188,
+// 239 MB, 76 us), the arithmetic of the short rows being the other half of
+// the deep levels' time.  Against one workgroup per box vector and 16 lanes for
+// every row, whole applies: 512 x 512 with 8 vectors 2.38 -> 1.9 ms, its
+// transpose (unfused before) 2.66 -> 1.9 ms; 384 x 384, FP64, 3 vectors 1.26 -> 1.14.
+//
+// PASS 0, up (Algorithm 2's upward step): input [rt_a; rt_b] (2c),
+//   q = [L^T rt_a; R^T rt_b], y = W' q, t = in - [S_a L y1; S_b R y2],
+//   out = U_l^T t (k).
+// PASS 1, down: wt (k) and the children's rt (2c),
+//   u = U_l wt, d = rt - diag(S_a, S_b) u, o = X_tau d (as above),
+//   out = [G_ab o_b; G_ba o_a] + u.
+// PASS 2, the down step transposed (leaves upward): wc (2c),
+//   vb = [G_ab wc_b; G_ba wc_a] (kept for PASS 3), t = X_tau^T vb, with
+//   X_tau^T v = v - [L z_1; R z_2], z = W'^T [(S_a L)^T v_a; (S_b R)^T v_b],
+//   out = U_l^T (wc - diag(S_a, S_b)^T t) (k).
+// PASS 3, the up step transposed: rb (k) and vb,
+//   out = X_tau^T (vb + U_l rb) (2c).
 template <typename R>
-static void level_check(const LevelApply<R>& A, int nvec) {
+constexpr int LVL_P = sizeof(R) == 4 ? 2 : 1;
+
+// LDS entries of one box vector
+__host__ __device__ inline int level_lds(int pass, int c, int k, int r) {
+  return pass == 0 ? 2 * c + 4 * r : pass == 1 ? k + 4 * c + 4 * r : pass == 2 ? 6 * c + 4 * r : k + 2 * c + 4 * r;
+}
+
+template <typename R, int NT, int NV, int PASS>
+__global__ __launch_bounds__(NT) void k_level(LevelApply<R> A, const cplx<R>* __restrict__ in,
+                                              const cplx<R>* __restrict__ in2, cplx<R>* __restrict__ out,
+                                              cplx<R>* __restrict__ out2, int nrhs) {
+  constexpr int P = LVL_P<R>;
+  extern __shared__ __align__(16) unsigned char lvl_lds[];
+  const int c = A.c, k = A.k, r = A.r, nb = A.nb, c2 = 2 * c, r2 = 2 * r;
+  const int b = blockIdx.x % nb, q0 = blockIdx.x / nb * NV;
+  const int nv = nrhs - q0 < NV ? nrhs - q0 : NV;
+  const long cr = (long)c * r, cc = (long)c * c;
+  cplx<R>* lds = reinterpret_cast<cplx<R>*>(lvl_lds);
+  auto vec = [&](int v) { return (long)(q0 + v) * nb + b; };
+  // copy of n entries per vector from global memory (zero for absent vectors)
+  auto stage = [&](cplx<R>* dst, const cplx<R>* src, int n) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+      for (int i = threadIdx.x; i < n; i += NT) dst[v * n + i] = v < nv ? src[vec(v) * n + i] : mk<R>(0, 0);
+  };
+  const BoxProd<R> mQ(A.Q, r, c, 2, r * c), mW(A.Ci + b * 4L * r * r, r2, r2, 1, 0);
+  const BoxProd<R> mS(A.S + 2 * cc * b, c, c, 2, c * c), mL(A.Q, c, r, 2, r * c);  // (PASS 2, 3: Q holds [L; R])
+  const BoxProd<R> mP(A.Pa + 2 * cr * b, PASS < 2 ? c : r, PASS < 2 ? r : c, 2, r * c);
+  const BoxProd<R> mU(A.U, c2, k, 1, 0), mUt(A.Ut, k, c2, 1, 0), mG(A.Gab, c, c, 2, (int)(A.Gba - A.Gab));
+  BoxFrag<R, P> f0, f1;
+  if constexpr (PASS == 0) {
+    cplx<R>*xs = lds, *q = xs + NV * c2, *y = q + NV * r2;
+    box_first(f0, mQ);
+    box_first(f1, mW);
+    stage(xs, in, c2);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mQ, f0, xs, xs + c, c2, [&](int h, int i, int v, cplx<R> s) { q[v * r2 + h * r + i] = s; });
+    box_first(f0, mP);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mW, f1, q, q, r2, [&](int, int i, int v, cplx<R> s) { y[v * r2 + i] = s; });
+    box_first(f1, mUt);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mP, f0, y, y + r, r2, [&](int h, int i, int v, cplx<R> s) {
+      cplx<R>& t = xs[v * c2 + h * c + i];
+      t = t - s;
+    });
+    __syncthreads();
+    box_run<R, P, NT, NV>(mUt, f1, xs, xs, c2, [&](int, int i, int v, cplx<R> s) {
+      if (v < nv) out[vec(v) * k + i] = s;
+    });
+  } else if constexpr (PASS == 1) {
+    cplx<R>*w = lds, *u = w + NV * k, *d = u + NV * c2, *q = d + NV * c2, *y = q + NV * r2;
+    box_first(f0, mU);
+    box_first(f1, mS);
+    stage(w, in, k);
+    stage(d, in2, c2);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mU, f0, w, w, k, [&](int, int i, int v, cplx<R> s) { u[v * c2 + i] = s; });
+    box_first(f0, mQ);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mS, f1, u, u + c, c2, [&](int h, int i, int v, cplx<R> s) {
+      cplx<R>& t = d[v * c2 + h * c + i];
+      t = t - s;
+    });
+    box_first(f1, mW);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mQ, f0, d, d + c, c2, [&](int h, int i, int v, cplx<R> s) { q[v * r2 + h * r + i] = s; });
+    box_first(f0, mP);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mW, f1, q, q, r2, [&](int, int i, int v, cplx<R> s) { y[v * r2 + i] = s; });
+    box_first(f1, mG);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mP, f0, y, y + r, r2, [&](int h, int i, int v, cplx<R> s) {
+      cplx<R>& t = d[v * c2 + h * c + i];
+      t = t - s;
+    });
+    __syncthreads();
+    box_run<R, P, NT, NV>(mG, f1, d + c, d, c2, [&](int h, int i, int v, cplx<R> s) {
+      if (v < nv) out[vec(v) * c2 + h * c + i] = s + u[v * c2 + h * c + i];
+    });
+  } else if constexpr (PASS == 2) {
+    cplx<R>*w = lds, *vb = w + NV * c2, *t = vb + NV * c2, *q = t + NV * c2, *y = q + NV * r2;
+    box_first(f0, mG);
+    box_first(f1, mP);
+    stage(w, in, c2);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mG, f0, w + c, w, c2, [&](int h, int i, int v, cplx<R> s) {
+      vb[v * c2 + h * c + i] = s;
+      if (v < nv) out2[vec(v) * c2 + h * c + i] = s;
+    });
+    box_first(f0, mW);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mP, f1, vb, vb + c, c2, [&](int h, int i, int v, cplx<R> s) { q[v * r2 + h * r + i] = s; });
+    box_first(f1, mL);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mW, f0, q, q, r2, [&](int, int i, int v, cplx<R> s) { y[v * r2 + i] = s; });
+    box_first(f0, mS);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mL, f1, y, y + r, r2, [&](int h, int i, int v, cplx<R> s) {
+      t[v * c2 + h * c + i] = vb[v * c2 + h * c + i] - s;
+    });
+    box_first(f1, mUt);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mS, f0, t, t + c, c2, [&](int h, int i, int v, cplx<R> s) {
+      cplx<R>& x = w[v * c2 + h * c + i];
+      x = x - s;
+    });
+    __syncthreads();
+    box_run<R, P, NT, NV>(mUt, f1, w, w, c2, [&](int, int i, int v, cplx<R> s) {
+      if (v < nv) out[vec(v) * k + i] = s;
+    });
+  } else {
+    cplx<R>*w = lds, *t = w + NV * k, *q = t + NV * c2, *y = q + NV * r2;
+    box_first(f0, mU);
+    box_first(f1, mP);
+    stage(w, in, k);
+    stage(t, in2, c2);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mU, f0, w, w, k, [&](int, int i, int v, cplx<R> s) {
+      cplx<R>& x = t[v * c2 + i];
+      x = x + s;
+    });
+    box_first(f0, mW);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mP, f1, t, t + c, c2, [&](int h, int i, int v, cplx<R> s) { q[v * r2 + h * r + i] = s; });
+    box_first(f1, mL);
+    __syncthreads();
+    box_run<R, P, NT, NV>(mW, f0, q, q, r2, [&](int, int i, int v, cplx<R> s) { y[v * r2 + i] = s; });
+    __syncthreads();
+    box_run<R, P, NT, NV>(mL, f1, y, y + r, r2, [&](int h, int i, int v, cplx<R> s) {
+      if (v < nv) out[vec(v) * c2 + h * c + i] = t[v * c2 + h * c + i] - s;
+    });
+  }
+}
+
+template <typename R, int PASS>
+static void level_launch(hipStream_t s, const LevelApply<R>& A, const cplx<R>* in, const cplx<R>* in2, cplx<R>* out,
+                         cplx<R>* out2, int nvec) {
   LSH_REQUIRE(A.c > 0 && A.k > 0 && A.r > 0 && A.nb > 0 && nvec > 0 && nvec % A.nb == 0, -6,
               "fused level apply: bad sizes");
-  LSH_REQUIRE((size_t)(A.k + 6 * A.c + 4 * A.r) * sizeof(cplx<R>) <= LEVEL_FUSED_LDS, -6,
-              "fused level apply: the box vectors exceed the workgroup's LDS");
+  const size_t one = (size_t)level_lds(PASS, A.c, A.k, A.r) * sizeof(cplx<R>);
+  LSH_REQUIRE(one <= LEVEL_FUSED_LDS, -6, "fused level apply: the box vectors exceed the workgroup's LDS");
+  const double e = (double)sizeof(cplx<R>), c = A.c, k = A.k, r = A.r;
+  static const char* name[2][4] = {{"level_up_f32", "level_down_f32", "level_tup_f32", "level_tdown_f32"},
+                                   {"level_up_f64", "level_down_f64", "level_tup_f64", "level_tdown_f64"}};
+  const bool square = PASS == 1 || PASS == 2;  // the S and G products
+  ProfScope ps(name[sizeof(R) == 8][PASS], s,
+               e * ((double)A.nb * (4 * r * r + 2 * c * r + (square ? 2 * c * c : 0)) + 2 * r * c + 2 * c * k +
+                    (square ? 2 * c * c : 0) + (double)nvec * (k + (PASS == 0 ? 2 : 4) * c)));
+  // right-hand sides per workgroup: as many (4, 2 or 1) as leave a workgroup
+  // per compute unit and fit the LDS; then threads for about 8192 waves in all
+  const int nrhs = nvec / A.nb;
+  int nv = nrhs >= 3 ? 4 : nrhs;
+  while (nv > 1 && (nv * one > LEVEL_FUSED_LDS || (long)A.nb * ((nrhs + nv - 1) / nv) < 256)) nv /= 2;
+  const int grid = A.nb * ((nrhs + nv - 1) / nv), nt = grid <= 512 ? 1024 : grid <= 1024 ? 512 : grid <= 2048 ? 256 : grid <= 4096 ? 128 : 64;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(nt), nv * one, s, A, in, in2, out, out2, nrhs);
+  };
+#define LSH_LEVEL(NT)                             \
+  case NT:                                        \
+    if (nv == 4) go(k_level<R, NT, 4, PASS>);     \
+    else if (nv == 2) go(k_level<R, NT, 2, PASS>); \
+    else go(k_level<R, NT, 1, PASS>);             \
+    break;
+  switch (nt) { LSH_LEVEL(1024) LSH_LEVEL(512) LSH_LEVEL(256) LSH_LEVEL(128) LSH_LEVEL(64) }
+#undef LSH_LEVEL
+  LSH_LAUNCH_CHECK();
+}
+
+template <typename R>
+bool level_fits(int c, int k, int r, bool transposed) {
+  const int n = transposed ? std::max(level_lds(2, c, k, r), level_lds(3, c, k, r))
+                           : std::max(level_lds(0, c, k, r), level_lds(1, c, k, r));
+  return (size_t)n * sizeof(cplx<R>) <= LEVEL_FUSED_LDS;
 }
 
 template <typename R>
 void level_up_fused(hipStream_t s, const LevelApply<R>& A, const cplx<R>* in, cplx<R>* out, int nvec) {
-  level_check(A, nvec);
-  const double e = (double)sizeof(cplx<R>);
-  ProfScope ps(sizeof(R) == 4 ? "level_up_f32" : "level_up_f64", s,
-               e * ((double)A.nb * (4.0 * A.r * A.r + 2.0 * A.c * A.r) + 2.0 * A.r * A.c + 2.0 * A.c * A.k +
-                    (double)nvec * (2.0 * A.c + A.k)));
-  const size_t lds = (size_t)(4 * A.c + 4 * A.r) * sizeof(cplx<R>);
-  const int nt = level_threads(nvec);
-  if (nt == 1024) hipLaunchKernelGGL((k_level_up<R, 1024>), dim3(nvec), dim3(1024), lds, s, A, in, out);
-  else if (nt == 512) hipLaunchKernelGGL((k_level_up<R, 512>), dim3(nvec), dim3(512), lds, s, A, in, out);
-  else hipLaunchKernelGGL((k_level_up<R, 256>), dim3(nvec), dim3(256), lds, s, A, in, out);
-  LSH_LAUNCH_CHECK();
+  level_launch<R, 0>(s, A, in, nullptr, out, nullptr, nvec);
 }
-
 template <typename R>
 void level_down_fused(hipStream_t s, const LevelApply<R>& A, const cplx<R>* wt, const cplx<R>* rtc, cplx<R>* wc,
                       int nvec) {
-  level_check(A, nvec);
-  const double e = (double)sizeof(cplx<R>);
-  ProfScope ps(sizeof(R) == 4 ? "level_down_f32" : "level_down_f64", s,
-               e * ((double)A.nb * (2.0 * A.c * A.c + 4.0 * A.r * A.r + 2.0 * A.c * A.r) + 2.0 * A.c * A.k +
-                    2.0 * A.r * A.c + 2.0 * A.c * A.c + (double)nvec * (A.k + 4.0 * A.c)));
-  const size_t lds = (size_t)(A.k + 6 * A.c + 4 * A.r) * sizeof(cplx<R>);
-  const int nt = level_threads(nvec);
-  if (nt == 1024) hipLaunchKernelGGL((k_level_down<R, 1024>), dim3(nvec), dim3(1024), lds, s, A, wt, rtc, wc);
-  else if (nt == 512) hipLaunchKernelGGL((k_level_down<R, 512>), dim3(nvec), dim3(512), lds, s, A, wt, rtc, wc);
-  else hipLaunchKernelGGL((k_level_down<R, 256>), dim3(nvec), dim3(256), lds, s, A, wt, rtc, wc);
-  LSH_LAUNCH_CHECK();
+  level_launch<R, 1>(s, A, wt, rtc, wc, nullptr, nvec);
+}
+template <typename R>
+void level_tup_fused(hipStream_t s, const LevelApply<R>& A, const cplx<R>* wc, cplx<R>* vb, cplx<R>* wb, int nvec) {
+  level_launch<R, 2>(s, A, wc, nullptr, wb, vb, nvec);
+}
+template <typename R>
+void level_tdown_fused(hipStream_t s, const LevelApply<R>& A, const cplx<R>* rb, const cplx<R>* vb, cplx<R>* rbc,
+                       int nvec) {
+  level_launch<R, 3>(s, A, rb, vb, rbc, nullptr, nvec);
 }
 
 #define LSH_HBS_INST(R)                                                                                       \
@@ -1941,7 +2095,11 @@ void level_down_fused(hipStream_t s, const LevelApply<R>& A, const cplx<R>* wt, 
                              const cplx<R>*, z64*, const double*, double, const I2*, const I2*, int, int, int);    \
   template void level_up_fused<R>(hipStream_t, const LevelApply<R>&, const cplx<R>*, cplx<R>*, int);            \
   template void level_down_fused<R>(hipStream_t, const LevelApply<R>&, const cplx<R>*, const cplx<R>*, cplx<R>*, \
-                                    int);
+                                    int);                                                                    \
+  template void level_tup_fused<R>(hipStream_t, const LevelApply<R>&, const cplx<R>*, cplx<R>*, cplx<R>*, int); \
+  template void level_tdown_fused<R>(hipStream_t, const LevelApply<R>&, const cplx<R>*, const cplx<R>*,        \
+                                     cplx<R>*, int);                                                         \
+  template bool level_fits<R>(int, int, int, bool);
 LSH_HBS_INST(float)
 LSH_HBS_INST(double)
 

@@ -95,18 +95,23 @@ void leaf_down(hipStream_t s, const cplx<R>* X, const cplx<R>* UL, int mL, int k
                const cplx<R>* r, z64* q, const double* b, double kappa2, const I2* leaf_origin,
                const I2* leaf_pts, int nleaf, int n, int nrhs);
 
-// Apply, one Woodbury level in one launch per pass (a workgroup per box
-// vector, the intermediates in LDS).  Shared: U (2c x k), Ut (k x 2c),
-// Q = [L^T; R^T] (2r x c), Gab, Gba (c x c); per box b < nb: Ci = W' (2r x 2r)
-// and Pa = [S_a L; S_b R] (two c x r blocks); per child: S (c x c).  All
-// row-major and packed.  Box vector v belongs to box v mod nb.
+// Apply, one Woodbury level in one launch per pass (a workgroup per box and
+// group of up to four right-hand sides, the intermediates in LDS).  Shared: U
+// (2c x k), Ut (k x 2c), Q = [L^T; R^T] (2r x c), Gab, Gba (c x c); per box
+// b < nb: Ci = W' (2r x 2r) and Pa = [S_a L; S_b R] (two c x r blocks); per
+// child: S (c x c).  All row-major and packed.  Box vector v belongs to box v
+// mod nb.  The transposed passes take the transposes of Ci, Pa's blocks and S,
+// and Q = [L; R] (two c x r blocks).
 template <typename R>
 struct LevelApply {
   int c, k, r, nb;
   const cplx<R> *U, *Ut, *Q, *Gab, *Gba, *S, *Ci, *Pa;
 };
-// the LDS the box vectors of one workgroup may take (k + 6c + 4r entries)
+// the LDS the box vectors of one workgroup may take
 constexpr size_t LEVEL_FUSED_LDS = 64 * 1024;
+// whether one box vector fits it
+template <typename R>
+bool level_fits(int c, int k, int r, bool transposed);
 // out[v] (k) = U^T X_tau in[v] (in: [nvec][2c])
 template <typename R>
 void level_up_fused(hipStream_t s, const LevelApply<R>& A, const cplx<R>* in, cplx<R>* out, int nvec);
@@ -114,5 +119,12 @@ void level_up_fused(hipStream_t s, const LevelApply<R>& A, const cplx<R>* in, cp
 template <typename R>
 void level_down_fused(hipStream_t s, const LevelApply<R>& A, const cplx<R>* wt, const cplx<R>* rtc, cplx<R>* wc,
                       int nvec);
+// vb[v] (2c) = Ghat wc[v], wb[v] (k) = U^T (wc[v] - diag(S)^T X_tau^T vb[v])
+template <typename R>
+void level_tup_fused(hipStream_t s, const LevelApply<R>& A, const cplx<R>* wc, cplx<R>* vb, cplx<R>* wb, int nvec);
+// rbc[v] (2c) = X_tau^T (vb[v] + U rb[v])
+template <typename R>
+void level_tdown_fused(hipStream_t s, const LevelApply<R>& A, const cplx<R>* rb, const cplx<R>* vb, cplx<R>* rbc,
+                       int nvec);
 
 }  // namespace lsh

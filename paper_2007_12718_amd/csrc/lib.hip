@@ -1,9 +1,3 @@
-// Woodbury levels with at least this many box vectors (lsh_apply_fused_levels;
-// 0: never) whose box vectors fit one workgroup's LDS run each apply pass in
-// one launch (level_up_fused / level_down_fused) instead of six to seven.
-constexpr int kApplyFusedMin = 128;
-static int g_apply_fused_min = kApplyFusedMin;
-
 // Host orchestration and the C ABI (include/lsh.h).
 //
 // plan   : tree (Sec. 3.1-3.2), correction weights (Sec. 2.2), kernel table,
@@ -49,6 +43,20 @@ std::string names();
 }  // namespace lsh
 
 using namespace lsh;
+
+// Woodbury levels whose box vectors fit one workgroup's LDS run each apply pass
+// in one launch instead of four to seven (level_up_fused and its kin), by this
+// rule on c, the size of the children's skeletons, and the number of box
+// vectors.  One workgroup takes a box through the pass, so its products must
+// not be too large for one compute unit: to c = 128 the launches saved are
+// worth more even with a few boxes (apply on 64 x 64: 232 us unfused below 128
+// vectors, 141 fused; on 256 x 256: 398 against 371, and 412 with c = 188 and
+// 16 boxes fused as well), to c = 256 from 128 box vectors on (c = 252, 128
+// boxes: 160 us either way; 32 boxes with 8 right-hand sides: 150 against 193;
+// c = 377, 16 boxes with 8: 313 against 232).  lsh_apply_fused_levels sets one
+// threshold on the box vectors instead (0: never; -1: this rule).
+constexpr int kApplyFusedSmall = 128, kApplyFusedMost = 256, kApplyFusedMin = 128;
+static int g_apply_fused_min = -1;
 
 namespace {
 
@@ -1567,25 +1575,23 @@ void ensure_transposed(const lsh_plan_s& P, FactorData<R>& F, hipStream_t s) {
   F.has_T = true;
 }
 
-// Woodbury levels with at least this many box vectors (LSH_LEVEL_FUSED
-// overrides it) whose box vectors fit one workgroup's LDS run each pass in one
-// launch (level_up_fused / level_down_fused) instead of six to seven.
-int level_fused_min() {
-  static const int v = [] {
-    const char* e = std::getenv("LSH_LEVEL_FUSED");
-    return e && *e ? std::atoi(e) : 512;
-  }();
-  return v;
-}
-
+// Whether level l's apply passes run in one launch each, and its matrices.
 template <typename R>
-bool level_fused(const lsh_plan_s& P, FactorData<R>& F, int l, int B, LevelApply<R>& A) {
-  if (g_apply_fused_min <= 0 || B < g_apply_fused_min || l < 1 || l >= P.L || P.lev[l].ident || F.wr[l] <= 0)
-    return false;
+bool level_fused(const lsh_plan_s& P, FactorData<R>& F, int l, int B, LevelApply<R>& A, bool transposed = false) {
+  if (g_apply_fused_min == 0 || l < 1 || l >= P.L || P.lev[l].ident || F.wr[l] <= 0) return false;
   const int c = P.lev[l].c, k = P.lev[l].k, r = F.wr[l];
-  if ((size_t)(k + 6 * c + 4 * r) * sizeof(cplx<R>) > LEVEL_FUSED_LDS) return false;
-  A = {c, k, r, 1 << l, P.U<R>(l), P.Ut<R>(l), P.W<R>(l, 1), P.Gab<R>(l), P.Gabt<R>(l),
-       F.S[l + 1].template as<cplx<R>>(), F.Ci[l].template as<cplx<R>>(), F.Pa[l].template as<cplx<R>>()};
+  if (!level_fits<R>(c, k, r, transposed)) return false;
+  // (the kernels reach both sibling blocks from the first with 32-bit offsets)
+  if (std::llabs((long long)(P.Gabt<R>(l) - P.Gab<R>(l))) > (1LL << 27)) return false;
+  if (g_apply_fused_min > 0 ? B < g_apply_fused_min
+                            : c > kApplyFusedSmall && (c > kApplyFusedMost || B < kApplyFusedMin))
+    return false;
+  if (transposed)
+    A = {c, k, r, 1 << l, P.U<R>(l), P.Ut<R>(l), P.W<R>(l, 0), P.Gab<R>(l), P.Gabt<R>(l),
+         F.ST[l + 1].template as<cplx<R>>(), F.CiT[l].template as<cplx<R>>(), F.PaT[l].template as<cplx<R>>()};
+  else
+    A = {c, k, r, 1 << l, P.U<R>(l), P.Ut<R>(l), P.W<R>(l, 1), P.Gab<R>(l), P.Gabt<R>(l),
+         F.S[l + 1].template as<cplx<R>>(), F.Ci[l].template as<cplx<R>>(), F.Pa[l].template as<cplx<R>>()};
   return true;
 }
 
@@ -1678,6 +1684,11 @@ void apply_MT(const lsh_plan_s& P, const double* b, FactorData<R>& F, const z64*
     const long cc = (long)c * c;
     const cplx<R>* wc = F.wt[l + 1].template as<cplx<R>>();
     cplx<R>* vb = F.vb[l].template as<cplx<R>>();
+    LevelApply<R> A;
+    if (level_fused(P, F, l, B, A, true)) {
+      level_tup_fused<R>(s, A, wc, vb, F.wt[l].template as<cplx<R>>(), B);
+      continue;
+    }
     // vb = Ghat wc
     if (B <= skinny<R>()) {  // both blocks in one launch
       cmgemv2<R>(s, 2 * c, c, -c, c, one, P.Gab<R>(l), c, wc + c, 2 * c, zero, nullptr, 0, vb, 2 * c, B,
@@ -1707,6 +1718,11 @@ void apply_MT(const lsh_plan_s& P, const double* b, FactorData<R>& F, const z64*
   for (int l = 1; l <= L - 1; ++l) {
     const int c = P.lev[l].c, k = P.lev[l].k, nb = 1 << l, B = nrhs * nb;
     const cplx<R>* vb = F.vb[l].template as<cplx<R>>();
+    LevelApply<R> A;
+    if (level_fused(P, F, l, B, A, true)) {
+      level_tdown_fused<R>(s, A, F.rt[l].template as<cplx<R>>(), vb, F.rt[l + 1].template as<cplx<R>>(), B);
+      continue;
+    }
     shared_mv<R>(s, 2 * c, k, one, P.U<R>(l), P.U<R>(l), k, OP_T, F.rt[l].template as<cplx<R>>(), k, one, vb, 2 * c,
                  t1, 2 * c, B, F.tk, P.lev[l].ident);
     apply_X<R>(P, F, l, nrhs, t1, F.rt[l + 1].template as<cplx<R>>(), s, true);
@@ -3727,7 +3743,7 @@ int lsh_fused_levels(int min_boxes) {
 int lsh_apply_fused_levels(int min_vectors) {
   API_BEGIN
   LSH_REQUIRE(min_vectors >= -1, LSH_ERR_INVALID_ARG, "min_vectors must be >= -1");
-  g_apply_fused_min = min_vectors < 0 ? kApplyFusedMin : min_vectors;
+  g_apply_fused_min = min_vectors;
   return LSH_OK;
   API_END
 }
