@@ -563,49 +563,63 @@ __global__ void k_gather_rows(const z64* Lt, int m, const int* rest, int nr, int
   Lr[e] = Lt[(long)t * m + rest[r]];
 }
 
-// D[q] = diagonal block q of L11 (nb x nb), identity-padded past k
 // Inverses of the 64 x 64 lower-triangular diagonal blocks of L11 (the last
-// block padded with the identity) by forward substitution, one workgroup per
-// block.  The four lanes of a quad share column c of the inverse, lane part
-// holding rows 16 part .. 16 part + 15; step q finishes X[q][c] and passes it
-// along the quad, whose later rows subtract L[r][q] X[q][c].
+// block padded with the identity), one workgroup per block, in LDS: the four
+// 16 x 16 diagonal blocks by forward substitution, a thread per column with
+// the column in registers, then joined by doubling (inv [[A, 0], [B, C]] =
+// [[A^-1, 0], [-C^-1 B A^-1, C^-1]]).  Bound by its chain of LDS latencies:
+// 16 dependent steps and four barriers instead of 64 steps with a lane
+// exchange each: TRI_MEASURED.
 constexpr int TRI_B = 64;
 __global__ __launch_bounds__(256) void k_trinv_blocks(const z64* L11, int k, z64* Dinv) {
-  __shared__ z64 Ls[TRI_B][TRI_B];
-  __shared__ z64 rd[TRI_B];  // 1 / L[q][q]
+  constexpr int S = 16, LD = TRI_B + 1;
+  __shared__ z64 X[TRI_B][LD];
+  __shared__ z64 T[32][33];
   const int tid = threadIdx.x, base = blockIdx.x * TRI_B;
   for (int e = tid; e < TRI_B * TRI_B; e += 256) {
     const int r = e / TRI_B, c = e % TRI_B, gi = base + r, gj = base + c;
     z64 v = mk(0.0, 0.0);
-    if (gi < k && gj < k) v = L11[(long)gi * k + gj];
+    if (gi < k && gj < k) v = r >= c ? L11[(long)gi * k + gj] : v;
     else if (r == c) v = mk(1.0, 0.0);
-    Ls[r][c] = v;
+    X[r][c] = v;
   }
   __syncthreads();
-  if (tid < TRI_B) rd[tid] = crecip(Ls[tid][tid]);
-  __syncthreads();
-  const int c = tid >> 2, part = tid & 3, lane = tid & 63;
-  z64 x[16];
+  if (tid < TRI_B) {  // column tid % 16 of diagonal block tid / 16
+    const int o = tid & ~(S - 1), c = tid & (S - 1);
+    z64 x[S];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) x[i] = mk(16 * part + i == c ? 1.0 : 0.0, 0.0);
-  for (int q = 0; q < TRI_B; ++q) {
-    z64 xq = mk(0.0, 0.0);
+    for (int q = 0; q < S; ++q) {
+      z64 t = mk(q == c ? 1.0 : 0.0, 0.0);
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (16 * part + i == q) xq = x[i] * rd[q];
-    const int src = (lane & ~3) | (q >> 4);
-    xq.x = __shfl(xq.x, src);
-    xq.y = __shfl(xq.y, src);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int r = 16 * part + i;
-      if (r == q) x[i] = xq;
-      else if (r > q) x[i] = x[i] - Ls[r][q] * xq;
+      for (int r = 0; r < q; ++r) t = t - X[o + q][o + r] * x[r];
+      x[q] = t * crecip(X[o + q][o + q]);
     }
+    // (one wave: every column has been read before any is written)
+#pragma unroll
+    for (int q = 0; q < S; ++q) X[o + q][o + c] = x[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int h = S; h < TRI_B; h *= 2) {
+    // pairs (A at i0, C at i0 + h): T = B A^-1, then B <- -C^-1 T
+    const int np = TRI_B / (2 * h), tot = np * h * h;
+    for (int e = tid; e < tot; e += 256) {
+      const int q = e / (h * h), r = e / h % h, c = e % h, i0 = q * 2 * h;
+      z64 t = mk(0.0, 0.0);
+      for (int u = c; u < h; ++u) fma_acc(t, X[i0 + h + r][i0 + u], X[i0 + u][i0 + c]);
+      T[q * h + r][c] = t;
+    }
+    __syncthreads();
+    for (int e = tid; e < tot; e += 256) {
+      const int q = e / (h * h), r = e / h % h, c = e % h, i0 = q * 2 * h;
+      z64 t = mk(0.0, 0.0);
+      for (int u = 0; u <= r; ++u) fma_acc(t, X[i0 + h + r][i0 + h + u], T[q * h + u][c]);
+      X[i0 + h + r][i0 + c] = mk(-t.x, -t.y);
+    }
+    __syncthreads();
   }
   z64* D = Dinv + (long)blockIdx.x * TRI_B * TRI_B;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) D[(16 * part + i) * TRI_B + c] = x[i];
+  for (int e = tid; e < TRI_B * TRI_B; e += 256) D[e] = X[e / TRI_B][e % TRI_B];
 }
 
 // U[piv[a]] = e_a ; U[rest[r]] = X[r]
@@ -857,21 +871,27 @@ __global__ __launch_bounds__(256) void k_bp_sc(const z64* Lt, int m, const int* 
 //
 // Four waves: lane b of wave w holds rows 12w..12w+11 of column b of S in
 // registers, and every wave keeps all the Schur diagonals d_b (lane b).  Per
-// pivot p: the pivot's lanes write column t of the factor (rl * S[:, p],
-// zero in picked rows) to LDS, one barrier, then every lane updates its rows,
-// S[:, b] -= L[:, t] conj(L[b, t]), and d_b -= |L[b, t]|^2.  The next
-// pivot's search (a DPP maximum of d) is independent of the row updates, so
-// the two run interleaved.  Pivot keys hold the top 26 bits of d (sign,
-// exponent, 14 mantissa bits): diagonals within a relative 2^-14 of the
-// largest count as ties, won by the lower candidate.  L_PP^{-1} follows by
-// forward substitution inside each wave.
+// pivot p: the wave that holds row p writes column t of the factor (rl times
+// the row's conjugate, an entry per lane, zero in picked rows) to LDS, one
+// barrier, then every lane updates its rows, S[:, b] -= L[:, t] conj(L[b, t]),
+// and d_b -= |L[b, t]|^2.  The next pivot's search (a DPP maximum of d) is
+// independent of the row updates, so the two run interleaved.  Pivot keys hold
+// the top 26 bits of d (sign, exponent, 14 mantissa bits): diagonals within a
+// relative 2^-14 of the largest count as ties, won by the lower candidate.
+// L_PP^{-1} follows by forward substitution inside each wave.  Bound by the
+// pivots' chain of latencies: with the column written by the pivot's lane of
+// each wave (twelve writes of one lane) a step of 24 pivots at depth 700 took
+// 50 us, this way 33.  (Joining the partial sums above into this launch, and
+// the selection into the new-columns one, by the workgroup that ends last was
+// slower, n = 1024 111 against 103 ms a setup: each workgroup's device fence
+// writes its L2 back, beside the factor's products.)
 constexpr int BP_CW = 4, BP_CR = BP_B / BP_CW;  // waves, rows per wave
 __global__ __launch_bounds__(64 * BP_CW) void k_bp_chol(const z64* M, const z64* part, int m, double alpha, int* J,
                                                         int* st, z64* Lpp, z64* Linv) {
-  static_assert(BP_B <= 64 && BP_NP == 32 && BP_B % BP_CW == 0 && BP_CW * 8 == BP_NP,
+  static_assert(BP_B <= 64 && BP_NP == 32 && BP_CR == 12 && BP_CW * 8 == BP_NP,
                 "one lane per candidate; 8 columns of L_PP^{-1} per wave");
   __shared__ z64 Ss[BP_B][BP_B + 1];   // S_C
-  __shared__ z64 Lb[BP_B][BP_NP + 1];  // factor columns for every candidate row
+  __shared__ z64 Lb[BP_NP][BP_B + 1];  // factor columns for every candidate row: [column][row]
   __shared__ z64 xs[BP_NP][BP_NP + 1]; // L_PP^{-1}
   __shared__ double rlv[BP_NP];        // 1 / L[t][t]
   __shared__ int piv[BP_NP];
@@ -941,23 +961,33 @@ __global__ __launch_bounds__(64 * BP_CW) void k_bp_chol(const z64* M, const z64*
     rl = rl * (1.5 - 0.5 * dp * rl * rl);
     rl = rl * (1.5 - 0.5 * dp * rl * rl);
     const double lpp = dp * rl;
-    if (b == p) {
-#pragma unroll
-      for (int i = 0; i < BP_CR; ++i) {
-        const int a = r0 + i;
-        const bool zero = (picked >> a) & 1ull;
-        z64 v = rl * col[i];
-        v.x = a == p ? lpp : (zero ? 0.0 : v.x);
-        v.y = (a == p || zero) ? 0.0 : v.y;
-        Lb[a][t] = v;
+    // column t of the factor from row p of S (S is Hermitian), one entry per
+    // lane of the wave that holds the row: one LDS write instead of twelve by
+    // a single lane
+    if (w == p / BP_CR) {
+      z64 v = mk(0.0, 0.0);
+      const int ip = __builtin_amdgcn_readfirstlane(p - r0);
+      switch (ip) {
+#define LSH_ROW(I) \
+  case I:          \
+    v = col[I];    \
+    break;
+        LSH_ROW(0) LSH_ROW(1) LSH_ROW(2) LSH_ROW(3) LSH_ROW(4) LSH_ROW(5) LSH_ROW(6) LSH_ROW(7) LSH_ROW(8)
+        LSH_ROW(9) LSH_ROW(10) LSH_ROW(11)
+#undef LSH_ROW
       }
-      if (w == 0) {
+      v = rl * conjg(v);
+      const bool zero = (picked >> b) & 1ull;
+      v.x = b == p ? lpp : (zero ? 0.0 : v.x);
+      v.y = (b == p || zero) ? 0.0 : v.y;
+      if (b < BP_B) Lb[t][b] = v;
+      if (b == 0) {
         rlv[t] = rl;
         piv[t] = p;
       }
     }
     __syncthreads();
-    const z64 clb = conjg(Lb[b < BP_B ? b : 0][t]);
+    const z64 clb = conjg(Lb[t][b < BP_B ? b : 0]);
     d -= abs2(clb);
     if (b == p) d = 0.0;
     picked |= 1ull << p;
@@ -967,7 +997,7 @@ __global__ __launch_bounds__(64 * BP_CW) void k_bp_chol(const z64* M, const z64*
     // alpha-greedy over all rows) and this pivot's row updates
     const int pn = pick();
 #pragma unroll
-    for (int i = 0; i < BP_CR; ++i) col[i] = col[i] - Lb[r0 + i][t] * clb;
+    for (int i = 0; i < BP_CR; ++i) col[i] = col[i] - Lb[t][r0 + i] * clb;
     dp = (pn >= 0 && pn < nc) ? readlane_f64(d, pn) : 0.0;
     go = pn >= 0 && pn < nc && dp > thr2 && dp >= dout;
     p = pn;
@@ -999,7 +1029,7 @@ __global__ __launch_bounds__(64 * BP_CW) void k_bp_chol(const z64* M, const z64*
 #pragma unroll
       for (int i = 0; i < BP_NP / 8; ++i) {
         const int r = k + 8 * i;
-        if (r > q && r < np) acc[i] = acc[i] - Lb[pr[i]][q] * xq;
+        if (r > q && r < np) acc[i] = acc[i] - Lb[q][pr[i]] * xq;
       }
     }
   }
@@ -1007,7 +1037,7 @@ __global__ __launch_bounds__(64 * BP_CW) void k_bp_chol(const z64* M, const z64*
   for (int e = tid; e < BP_NP * BP_NP; e += 64 * BP_CW) {
     const int q = e / BP_NP, r = e % BP_NP;
     const bool in = q < np && r <= q;
-    Lpp[e] = in ? Lb[piv[q]][r] : mk(0.0, 0.0);
+    Lpp[e] = in ? Lb[r][piv[q]] : mk(0.0, 0.0);
     Linv[e] = in ? xs[q][r] : mk(0.0, 0.0);
   }
   if (w == 0) {
@@ -1322,12 +1352,12 @@ int rowid_bp(hipStream_t s, const z64* A, int m, int np, double tol, double alph
   hipLaunchKernelGGL(k_bp_thr2, dim3(1), dim3(1024), 0, s, d, m, tol * tol, st);
   LSH_LAUNCH_CHECK();
   const int gm = ceil_div(m, 256);
-  // steps in batches; the first batches are short (the first step alone
-  // can take every pivot of a small block).  With a parent Gram to feed, at
-  // most 16 steps a batch, so that its last rows (after the final step) are
-  // few.
+  // steps in batches of four, then eight: a batch costs one read-back (about
+  // 20 us with the queue empty), a step queued after the end about 10 us, and
+  // the parent's Gram rows start after each batch (n = 1024: 100.3 ms a setup
+  // with batches up to 8, 103.2 with 16 and, without a parent, 32)
   int batch = 4, host_st[4] = {0, 0, 0, 0};
-  const int max_batch = next ? 16 : 32;
+  constexpr int max_batch = 8;
   while (true) {
     for (int b = 0; b < batch; ++b) {
       {
