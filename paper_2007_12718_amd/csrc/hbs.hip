@@ -654,7 +654,7 @@ __global__ void k_scatter_U(z64* U, int k, const int* piv, const int* rest, int 
 // pivot count, done flag) lives on the device: the host queues steps in
 // batches and reads the done flag once per batch; a step queued after the
 // end returns at entry.
-constexpr int BP_B = 48, BP_NP = 32, BP_KC = 128, BP_KCS = 64, BP_SUB = 32, BP_SEL = 16384;
+constexpr int BP_B = 48, BP_NP = 32, BP_KCMAX = 128, BP_KCS = 64, BP_SEL = 16384;
 // state words (int): 0 rank j, 1 done, 2 pivots of this step, 3 candidates,
 // 4..5 dout (double), 6 error flag, 8..8+BP_B candidate rows, 120..121 the
 // stopping threshold thr2 (double)
@@ -814,52 +814,64 @@ __global__ __launch_bounds__(1024) void k_bp_select(const double* d, const int* 
   }
 }
 
-// S_C partial sums: blockIdx.x = depth chunk c (BP_KCS deep, staged BP_SUB
-// at a time), blockIdx.y = output quadrant (rows a0.., columns b0.., each
-// BP_B / 2 wide): part[c][a][b] = sum_{t in chunk, t < j} L(C_a, t) conj(L(C_b, t)).
+// S_C partial sums: blockIdx.x = depth chunk c (BP_KCS deep), blockIdx.y =
+// output quadrant (rows a0.., columns b0.., each BP_B / 2 wide):
+// part[c][a][b] = sum_{t in chunk, t < j} L(C_a, t) conj(L(C_b, t)).  The chunk
+// is staged at once; a lane of each of the four waves takes 3 x 3 outputs (six
+// LDS reads for nine products; LDS bandwidth bounds the kernel, after the
+// staging's latency) over a quarter of the depth, and the waves' sums meet in
+// LDS.  With one output at a time per thread and two stagings: 14 us a step at
+// depth 700, this way 12.
 __global__ __launch_bounds__(256) void k_bp_sc(const z64* Lt, int m, const int* st, z64* part) {
-  constexpr int H = BP_B / 2, PER = (H * H + 255) / 256;
-  __shared__ z64 La[BP_SUB][H + 1], Lb2[BP_SUB][H + 1];
+  constexpr int H = BP_B / 2, Q = BP_KCS / 4;
+  static_assert(H == 24, "64 lanes of 3 x 3 outputs");
+  __shared__ z64 stage[2][BP_KCS][H + 1];
+  static_assert(2 * BP_KCS * (H + 1) >= 4 * H * H, "the waves' sums fit the staging");
+  z64(*La)[H + 1] = stage[0];
+  z64(*Lb2)[H + 1] = stage[1];
   if (st[BPS_DONE]) return;
   const int j = st[BPS_J], nc = st[BPS_NC];
   const int c = blockIdx.x, t0 = c * BP_KCS;
   if (t0 >= j) return;
   const int a0 = (blockIdx.y >> 1) * H, b0 = (blockIdx.y & 1) * H;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int* cand = st + BPS_CAND;
-  z64 acc[PER];
-#pragma unroll
-  for (int r = 0; r < PER; ++r) acc[r] = mk(0.0, 0.0);
-  const int tend = (j - t0) < BP_KCS ? j : t0 + BP_KCS;
-  for (int s0 = t0; s0 < tend; s0 += BP_SUB) {
-    __syncthreads();
-    for (int e = tid; e < 2 * BP_SUB * H; e += 256) {
-      const int half = e / (BP_SUB * H), f = e % (BP_SUB * H), t = f / H, a = f % H;
-      const int row = (half ? b0 : a0) + a;
-      const z64 v = (row < nc && s0 + t < tend) ? Lt[(long)(s0 + t) * m + cand[row]] : mk(0.0, 0.0);
-      if (half) Lb2[t][a] = v;
-      else La[t][a] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-      const int e = tid + r * 256;
-      if (e < H * H) {
-        const int a = e / H, b = e % H;
-        z64 v = acc[r];
-        for (int t = 0; t < BP_SUB; ++t) v = v + La[t][a] * conjg(Lb2[t][b]);
-        acc[r] = v;
-      }
-    }
+  for (int e = tid; e < 2 * BP_KCS * H; e += 256) {
+    const int half = e / (BP_KCS * H), f = e % (BP_KCS * H), t = f / H, a = f % H;
+    const int row = (half ? b0 : a0) + a;
+    const z64 v = (row < nc && t0 + t < j) ? Lt[(long)(t0 + t) * m + cand[row]] : mk(0.0, 0.0);
+    if (half) Lb2[t][a] = conjg(v);
+    else La[t][a] = v;
   }
+  __syncthreads();
+  const int ta = lane >> 3, tb = lane & 7;  // outputs ta + 8 i, tb + 8 k
+  z64 acc[3][3];
 #pragma unroll
-  for (int r = 0; r < PER; ++r) {
-    const int e = tid + r * 256;
-    if (e < H * H) {
-      const int a = a0 + e / H, b = b0 + e % H;
-      part[(long)c * BP_B * BP_B + a * BP_B + b] = acc[r];
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) acc[i][k] = mk(0.0, 0.0);
+  for (int t = wave * Q; t < (wave + 1) * Q; ++t) {
+    z64 x[3], y[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      x[i] = La[t][ta + 8 * i];
+      y[i] = Lb2[t][tb + 8 * i];
     }
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) fma_acc(acc[i][k], x[i], y[k]);
   }
+  __syncthreads();
+  z64* red = &La[0][0];  // [wave][output]
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) red[wave * H * H + (ta + 8 * i) * H + tb + 8 * k] = acc[i][k];
+  __syncthreads();
+  for (int e = tid; e < H * H; e += 256)
+    part[(long)c * BP_B * BP_B + (a0 + e / H) * BP_B + b0 + e % H] =
+        (red[e] + red[H * H + e]) + (red[2 * H * H + e] + red[3 * H * H + e]);
 }
 
 // Greedy pivoted Cholesky of the candidate block S_C = M[C,C] - sum_c
@@ -1071,6 +1083,7 @@ __global__ __launch_bounds__(64 * BP_CW) void k_bp_chol(const z64* M, const z64*
 // a wave), and early steps have few depth chunks: small row blocks (JT = 1)
 // keep every unit busy then.
 constexpr int BP_WT_JT = 1, BP_WT_ROWS = 64 * BP_WT_JT;
+template <int BP_KC>
 __global__ __launch_bounds__(256) void k_bp_wt(const z64* Lt, const int* J, int m, const int* st, z64* part) {
   typedef double d4 __attribute__((ext_vector_type(4)));
   __shared__ double Apr[BP_NP][BP_KC + 1], Api[BP_NP][BP_KC + 1];
@@ -1177,13 +1190,13 @@ constexpr int BP_NCR = 32;
 static_assert(BP_NCR == BP_NP && BP_NCR * BP_NP == 1024, "one thread per (pivot, row) pair");
 __global__ __launch_bounds__(1024) void k_bp_newcols(z64* Lt, const z64* M, int m, const int* J, const z64* part,
                                                      const z64* Lpp, const z64* Linv, int* chosen, double* d,
-                                                     const int* st) {
+                                                     const int* st, int kc) {
   __shared__ z64 W[BP_NP][BP_NCR + 1];
   __shared__ z64 Li[BP_NP][BP_NP + 1];
   __shared__ double sd[BP_NP][BP_NCR + 1];
   if (st[BPS_DONE]) return;
   const int j = st[BPS_J], np = st[BPS_NP];
-  const int nch = (j + BP_KC - 1) / BP_KC;
+  const int nch = (j + kc - 1) / kc;
   const int tid = threadIdx.x, q = tid / BP_NCR, ii = tid % BP_NCR;
   const int i = blockIdx.x * BP_NCR + ii;
   const int* Pq = J + j;
@@ -1230,9 +1243,15 @@ __global__ __launch_bounds__(1024) void k_bp_newcols(z64* Lt, const z64* M, int 
   }
 }
 
+// depth of k_bp_wt's chunks: 64 up to 1536 candidates, where 128 would leave
+// units idle (at depth 700 of 750 candidates: 22 us a step with 128, 14 with
+// 64), 128 beyond, where the partial sums' bytes count (n = 1024: 98.5 ms a setup
+// with this line at 1536, 99.8 with 128 everywhere, 100 with 64 everywhere)
+static int bp_kc(int m) { return m <= 1536 ? 64 : 128; }
+
 size_t rowid_bp_ws(int m) {
-  const size_t mm = (size_t)m * m, mp = (size_t)m + BP_KC;
-  const size_t nch = mp / BP_KC + 1;
+  const size_t mm = (size_t)m * m, mp = (size_t)m + BP_KCMAX;
+  const size_t nch = mp / bp_kc(m) + 1;
   return sizeof(z64) * (mm + mp * m + 2 * mm) + sizeof(double) * m + sizeof(int) * (3 * m + BPS_WORDS) +
          sizeof(z64) * (BP_B * BP_B + 2 * BP_NP * BP_NP + (mp / BP_KCS + 1) * BP_B * BP_B +
                         nch * (size_t)BP_NP * m) +
@@ -1376,11 +1395,12 @@ int rowid_bp(hipStream_t s, const z64* A, int m, int np, double tol, double alph
       LSH_LAUNCH_CHECK();
       {
         ProfScope ps("bp_wt", s, 16.0 * m * m);
-        hipLaunchKernelGGL(k_bp_wt, dim3(ceil_div(m, BP_WT_ROWS), nch), dim3(256), 0, s, Lt, J, m, st, partW);
+        hipLaunchKernelGGL(kc == 64 ? k_bp_wt<64> : k_bp_wt<128>, dim3(ceil_div(m, BP_WT_ROWS), nch), dim3(256), 0, s,
+                           Lt, J, m, st, partW);
       }
       LSH_LAUNCH_CHECK();
       hipLaunchKernelGGL(k_bp_newcols, dim3(ceil_div(m, BP_NCR)), dim3(1024), 0, s, Lt, M, m, J, partW, Lpp, Linv,
-                         chosen, d, st);
+                         chosen, d, st, kc);
       LSH_LAUNCH_CHECK();
     }
     LSH_HIP(hipMemcpyAsync(host_st, st, sizeof(int) * 4, hipMemcpyDeviceToHost, s));
