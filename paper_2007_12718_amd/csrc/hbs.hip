@@ -1341,8 +1341,8 @@ int rowid_bp(hipStream_t s, const z64* A, int m, int np, double tol, double alph
   LSH_REQUIRE(m <= BP_SEL, -6, "row ID: more than 16384 candidate rows in one level");
   char* p = static_cast<char*>(ws);
   auto take = [&](size_t bytes) { char* r = p; p += ((bytes + 255) / 256) * 256; return (void*)r; };
-  const size_t mp = (size_t)m + BP_KC;
-  const int nch = (int)(mp / BP_KC) + 1, nchS = (int)(mp / BP_KCS) + 1;
+  const size_t mp = (size_t)m + BP_KCMAX;
+  const int kc = bp_kc(m), nch = (int)(mp / kc) + 1, nchS = (int)(mp / BP_KCS) + 1;
   z64* M = static_cast<z64*>(take(sizeof(z64) * (size_t)m * m));
   z64* Lt = static_cast<z64*>(take(sizeof(z64) * mp * m));
   z64* L11 = static_cast<z64*>(take(sizeof(z64) * (size_t)m * m));
