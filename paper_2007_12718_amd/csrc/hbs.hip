@@ -1280,15 +1280,15 @@ __global__ void k_place_diag(const z64* D, int k, z64* Linv) {
 // products), then U(rest) = L(rest) L11^{-1} is one product: a dozen wide
 // launches instead of a block-by-block substitution chain.  Linv (k x k) and
 // the pairs' temporaries T (at most k^2 / 4 entries) are scratch.
-static void gram_interp(hipStream_t s, const z64* Lt, int m, int k, int* J, z64* U, int* rest, z64* L11, z64* Lr,
-                        z64* Dinv, z64* Linv, z64* T) {
+// Jh: the skeleton on the host; rh receives the other rows (the upload's
+// source: it has to stay until the work on s is done).
+static void gram_interp(hipStream_t s, const z64* Lt, int m, int k, const int* Jh, std::vector<int>& rh, int* J,
+                        z64* U, int* rest, z64* L11, z64* Lr, z64* Dinv, z64* Linv, z64* T) {
   const int DB = 64;
-  std::vector<int> ph(k), rh;
-  LSH_HIP(hipMemcpyAsync(ph.data(), J, sizeof(int) * k, hipMemcpyDeviceToHost, s));
-  LSH_HIP(hipStreamSynchronize(s));
   {
     std::vector<char> used(m, 0);
-    for (int v : ph) used[v] = 1;
+    for (int q = 0; q < k; ++q) used[Jh[q]] = 1;
+    rh.clear();
     for (int i = 0; i < m; ++i)
       if (!used[i]) rh.push_back(i);
   }
@@ -1336,7 +1336,7 @@ static void gram_interp(hipStream_t s, const z64* Lt, int m, int k, int* J, z64*
 }
 
 int rowid_bp(hipStream_t s, const z64* A, int m, int np, double tol, double alpha, int* J, z64* U, void* ws,
-             bool gram_ready, NextGram* next, const std::function<void(int)>& on_skel) {
+             bool gram_ready, NextGram* next, const std::function<void(int)>& on_skel, BpInterp* later) {
   LSH_REQUIRE(alpha > 0.0 && alpha <= 1.0, -1, "row ID: alpha must lie in (0, 1]");
   LSH_REQUIRE(m <= BP_SEL, -6, "row ID: more than 16384 candidate rows in one level");
   char* p = static_cast<char*>(ws);
@@ -1426,15 +1426,29 @@ int rowid_bp(hipStream_t s, const z64* A, int m, int np, double tol, double alph
     LSH_HIP(hipStreamSynchronize(s));
     if (next) next_gram_rows(*next, J, 1);
     if (on_skel) on_skel(1);
+    if (later) later->m = 0;  // (U is complete)
     return 1;
   }
   if (next) next_gram_rows(*next, J, j);  // (J is final: the stream was synchronised)
   if (on_skel) on_skel(j);                // (before the interpolation matrix)
   // (the Gram is no longer needed: it holds L11^{-1}; the pairs' temporaries
   // follow the rest rows in Lr)
-  gram_interp(s, Lt, m, j, J, U, rest, L11, Lr, Dinv, M, Lr + (size_t)(m - j) * j);
+  const BpInterp I{Lt, m, j, J, rest, L11, Lr, Dinv, M, Lr + (size_t)(m - j) * j};
   (void)invws;
+  if (later) {
+    *later = I;
+    return j;
+  }
+  std::vector<int> ph(j), rh;
+  LSH_HIP(hipMemcpyAsync(ph.data(), J, sizeof(int) * j, hipMemcpyDeviceToHost, s));
+  LSH_HIP(hipStreamSynchronize(s));
+  bp_interp(s, I, ph.data(), rh, U);
+  LSH_HIP(hipStreamSynchronize(s));
   return j;
+}
+
+void bp_interp(hipStream_t s, const BpInterp& I, const int* Jh, std::vector<int>& rh, z64* U) {
+  gram_interp(s, I.Lt, I.m, I.k, Jh, rh, I.J, U, I.rest, I.L11, I.Lr, I.Dinv, I.Linv, I.T);
 }
 
 size_t rowid_gram_ws(int m) {
@@ -1499,7 +1513,11 @@ int rowid_gram(hipStream_t s, const z64* A, int m, int np, double tol, int* J, z
     rank = st[0];
   }
   const int k = rank < 1 ? 1 : rank;
-  gram_interp(s, Lt, m, k, J, U, rest, L11, Lr, Dinv, M, Lr + (size_t)(m - k) * k);
+  std::vector<int> ph(k), rh;
+  LSH_HIP(hipMemcpyAsync(ph.data(), J, sizeof(int) * k, hipMemcpyDeviceToHost, s));
+  LSH_HIP(hipStreamSynchronize(s));
+  gram_interp(s, Lt, m, k, ph.data(), rh, J, U, rest, L11, Lr, Dinv, M, Lr + (size_t)(m - k) * k);
+  LSH_HIP(hipStreamSynchronize(s));
   (void)invws;
   return k;
 }

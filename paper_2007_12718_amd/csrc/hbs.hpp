@@ -1,6 +1,7 @@
 // HBS compression / factor / apply kernels (host launchers).
 #pragma once
 #include <functional>
+#include <vector>
 #include "blas.hpp"
 
 namespace lsh {
@@ -68,8 +69,21 @@ void next_gram_pack(hipStream_t s, const NextGram& g, int k, z64* M);
 // Returns the rank (synchronises on the stream once per batch of steps).
 // on_skel(k), when given, runs once the skeleton J[0..k) is final on the
 // device (s synchronised), before the interpolation matrix U is formed.
+// later, when given, receives what the interpolation needs instead of U being
+// formed (in ws, which stays in use until bp_interp's work is done; m = 0 if U
+// is complete all the same).
+struct BpInterp {
+  const z64* Lt = nullptr;
+  int m = 0, k = 0;
+  int *J = nullptr, *rest = nullptr;
+  z64 *L11 = nullptr, *Lr = nullptr, *Dinv = nullptr, *Linv = nullptr, *T = nullptr;
+};
 int rowid_bp(hipStream_t s, const z64* A, int m, int np, double tol, double alpha, int* J, z64* U, void* ws,
-             bool gram_ready = false, NextGram* next = nullptr, const std::function<void(int)>& on_skel = {});
+             bool gram_ready = false, NextGram* next = nullptr, const std::function<void(int)>& on_skel = {},
+             BpInterp* later = nullptr);
+// U (m x k) of such a row ID; Jh: the skeleton on the host; rh is filled with
+// the other rows and has to stay until the work on s is done
+void bp_interp(hipStream_t s, const BpInterp& I, const int* Jh, std::vector<int>& rh, z64* U);
 size_t rowid_bp_ws(int m);
 
 // Leaf factor helpers (R = working precision)

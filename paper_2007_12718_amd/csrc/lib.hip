@@ -115,6 +115,28 @@ struct lsh_plan_s {
   // sgram holds the parent level's Gram rows built during a level's row ID
   // (rewound once they are packed into the parent's row-ID workspace).
   mem::Arena persist, sid, ssib, sgram;
+  // In lsh_build a level's interpolation matrix is formed beside the next
+  // level's row ID (interp_wait is set), so two levels' temporaries share sid:
+  // alternate levels lie at its two ends, sized by the actual candidates (sid
+  // is sized by bounds of about twice those, so four times the bytes).
+  // interp_wait(l) returns once level l's are free; false: the build failed.
+  std::function<bool(int)> interp_wait;
+  mem::Arena id_end[2];
+  size_t id_need[2] = {0, 0};
+  mem::Arena& id_arena(int l) { return interp_wait ? id_end[(l - d.full_levels) & 1] : sid; }
+  // the end of level l (of `need` bytes), once what lies there, and what would
+  // overlap it from the other end, is free
+  void place_level(int l, size_t need) {
+    const int e = (l - d.full_levels) & 1;
+    bool ok = l + 2 > L || interp_wait(l + 2);
+    if (ok && l < L && need + id_need[1 - e] > sid.cap()) ok = interp_wait(l + 1), id_need[1 - e] = 0;
+    if (!ok) throw Error(LSH_ERR_HIP, "internal: the build has failed elsewhere");
+    id_need[e] = need;
+    sid.reset(0);
+    (void)sid.take(id_need[0] + id_need[1]);  // (the high-water mark)
+    id_end[e].attach(e ? sid.base() + (sid.cap() - need) / mem::kGranule * mem::kGranule : sid.base(), need,
+                     "plan row-ID temporaries");
+  }
   // side stream for the parent Gram rows while a plan is built (null: the
   // Gram of each level is formed after its candidates are known)
   hipStream_t gs = nullptr;
@@ -124,6 +146,7 @@ struct lsh_plan_s {
   std::function<void(int)> skel_cb;
   NextGram ng;          // the parent Gram in progress or done
   int ng_level = -1;    // the level whose Gram ng holds (-1: none)
+  hipEvent_t ng_ev = nullptr;  // (lsh_build) the side stream has this level's parent Gram rows
   std::vector<I2> ng_prox;  // (host source of its proxy upload)
   ConvOperator op;
   // The row-ID temporaries (sid) are free once the plan is built; the receiver
@@ -276,12 +299,15 @@ int identity_id(int m, std::vector<int>& Jh, DevBuf& U64, hipStream_t s) {
 // the plan's tolerance: J to the host, U (m x k) to a new buffer of the
 // bound arena, temporaries from scr; returns k.  Synchronises s.
 //
+// later (block-pivoted path only): U is left to bp_interp, its inputs (in scr)
+// in *later (m = 0: U is there).
 // gram (block-pivoted path only): called with the row-ID workspace's Gram
 // block before the pivot steps; it may fill that block (ready = true: A is
 // then unused) and return the parent level's Gram rows to feed (or null).
 int row_id_matrix(lsh_plan_s& P, z64* A, int m, int np, std::vector<int>& Jh, DevBuf& U64, mem::Arena& scr,
                   hipStream_t s, const std::function<NextGram*(z64*, bool&)>& gram = {},
-                  const std::function<void(int)>& on_skel = {}) {
+                  const std::function<void(int)>& on_skel = {}, BpInterp* later = nullptr) {
+  if (later) later->m = 0;
   if (P.d.tol == 0) {  // exact full-rank form
     const int k = identity_id(m, Jh, U64, s);
     if (on_skel) on_skel(k);
@@ -318,7 +344,8 @@ int row_id_matrix(lsh_plan_s& P, z64* A, int m, int np, std::vector<int>& Jh, De
       void* ws = scr.take(rowid_bp_ws(m));
       bool ready = false;
       NextGram* next = gram ? gram(static_cast<z64*>(ws), ready) : nullptr;
-      k = rowid_bp(s, A, m, np, P.d.tol, alpha, J, Ufull, ws, ready, next, skel);
+      k = rowid_bp(s, A, m, np, P.d.tol, alpha, J, Ufull, ws, ready, next, skel, later);
+      if (later && later->m > 0) return k;
     }
   }
   if (!told) skel(k);
@@ -399,7 +426,8 @@ void skeleton_known(lsh_plan_s& P, int l) {
   if (P.skel_cb) P.skel_cb(top);
 }
 
-void level_id(lsh_plan_s& P, int l, Level& lv, const std::vector<I2>& prox, hipStream_t s) {
+void level_id(lsh_plan_s& P, int l, Level& lv, const std::vector<I2>& prox, hipStream_t s, BpInterp* later = nullptr) {
+  if (later) later->m = 0;
   const int m = lv.m, np = (int)prox.size();
   if (!lv.host_ready) lv.ident = P.d.tol == 0 || l <= P.d.full_levels;
   if (lv.ident) {  // every candidate kept (exact form, or an uncompressed top level)
@@ -415,12 +443,13 @@ void level_id(lsh_plan_s& P, int l, Level& lv, const std::vector<I2>& prox, hipS
   }
   const bool block = block_pivots(P);
   const bool pre = block && P.gs && P.ng_level == l && P.ng.done * 2 == m;
-  const I2* dc = upload_to(P.sid, lv.cand, s);
+  mem::Arena& tmp = P.id_arena(l);
+  const I2* dc = upload_to(tmp, lv.cand, s);
   const int ncols = P.hbs_order == 4 ? np : 2 * np;
   z64* A = nullptr;
   if (!pre) {
-    const I2* dp = upload_to(P.sid, prox, s);
-    A = static_cast<z64*>(P.sid.take(sizeof(z64) * (size_t)m * ncols));
+    const I2* dp = upload_to(tmp, prox, s);
+    A = static_cast<z64*>(tmp.take(sizeof(z64) * (size_t)m * ncols));
     gather_table(s, P.table.as<z64>(), P.D, dc, m, dp, np, A, ncols);
     // order > 4: the rows must also span the corrected entries against the
     // ring's points (the actual near neighbours, within the stencil's
@@ -460,11 +489,13 @@ void level_id(lsh_plan_s& P, int l, Level& lv, const std::vector<I2>& prox, hipS
     P.ng_level = l - 1;
     return &g;
   };
-  row_id_matrix(P, A, m, ncols, lv.J, lv.U64, P.sid, s, block ? gram : std::function<NextGram*(z64*, bool&)>(),
+  row_id_matrix(P, A, m, ncols, lv.J, lv.U64, tmp, s, block ? gram : std::function<NextGram*(z64*, bool&)>(),
                 [&](int k) {
                   lv.k = k;
+                  if (P.ng_ev && P.ng_level == l - 1) LSH_HIP(hipEventRecord(P.ng_ev, P.gs));
                   skeleton_known(P, l);
-                });
+                },
+                P.d.plan_cache ? nullptr : later);
   if (P.d.plan_cache) pcache::insert(key, lv.cand, lv.J, m, lv.k, lv.U64, s);
 }
 
@@ -560,38 +591,65 @@ void plan_interp_rows(lsh_plan_s& P, int l, hipStream_t s) {
   }
 }
 
-void plan_id(lsh_plan_s& P, int l, hipStream_t s) {
-  const lsh_desc& d = P.d;
-  const bool f32 = d.hbs_prec == LSH_FP32;
-  if (l >= 1) {  // row ID of level l (Sec. 3.2)
-    LSH_HIP(hipStreamSynchronize(s));
-    if (P.gs) LSH_HIP(hipStreamSynchronize(P.gs));  // (this level's Gram rows, read from the previous sid)
-    P.sid.reset(0);  // (the previous level's temporaries are no longer in use)
-    Level& lv = P.lev[l];
-    if (!lv.host_ready) {
-      if (l == P.L) {
-        lv.cand = P.leaf_pts_h;
-        lv.m = (int)lv.cand.size();
-      } else {
-        level_candidates(P, l, lv);
-      }
-    }
-    level_id(P, l, lv, proxy_ring(lv.sx, lv.sy, d.proxy_width), s);
-    if (!lv.skel_known) skeleton_known(P, l);
+// the copies of U_l that the factor and the apply read
+void plan_id_finish(lsh_plan_s& P, int l, hipStream_t s) {
+  const bool f32 = P.d.hbs_prec == LSH_FP32;
+  Level& lv = P.lev[l];
+  if (f32) {
+    lv.U32.alloc(sizeof(c32) * (size_t)lv.m * lv.k);
+    ccast<double, float>(s, lv.U64.as<z64>(), lv.U32.as<c32>(), (long)lv.m * lv.k);
+  }
+  if (!lv.ident) {  // (U = I is its own transpose: Ut(l) then reads U)
+    lv.Ut64.alloc(sizeof(z64) * (size_t)lv.m * lv.k);
+    ctranspose<double>(s, lv.U64.as<z64>(), lv.m, lv.k, lv.Ut64.as<z64>());
     if (f32) {
-      lv.U32.alloc(sizeof(c32) * (size_t)lv.m * lv.k);
-      ccast<double, float>(s, lv.U64.as<z64>(), lv.U32.as<c32>(), (long)lv.m * lv.k);
+      lv.Ut32.alloc(sizeof(c32) * (size_t)lv.m * lv.k);
+      ctranspose<float>(s, lv.U32.as<c32>(), lv.m, lv.k, lv.Ut32.as<c32>());
     }
-    if (!lv.ident) {  // (U = I is its own transpose: Ut(l) then reads U)
-      lv.Ut64.alloc(sizeof(z64) * (size_t)lv.m * lv.k);
-      ctranspose<double>(s, lv.U64.as<z64>(), lv.m, lv.k, lv.Ut64.as<z64>());
-      if (f32) {
-        lv.Ut32.alloc(sizeof(c32) * (size_t)lv.m * lv.k);
-        ctranspose<float>(s, lv.U32.as<c32>(), lv.m, lv.k, lv.Ut32.as<c32>());
-      }
-      if (l < P.L) plan_interp_rows(P, l, s);
+    if (l < P.L) plan_interp_rows(P, l, s);
+  }
+}
+
+size_t level_scratch_bytes(const lsh_desc& d, long m, long np, long ncols);
+
+// Row ID of level l (Sec. 3.2).  later: the level's interpolation matrix and
+// its copies may be left to plan_id_later (later->m > 0 then), on another
+// stream; the level's temporaries stay in use until it is done.
+void plan_id(lsh_plan_s& P, int l, hipStream_t s, BpInterp* later = nullptr) {
+  const lsh_desc& d = P.d;
+  if (later) later->m = 0;
+  if (l < 1) return;
+  LSH_HIP(hipStreamSynchronize(s));
+  Level& lv = P.lev[l];
+  if (!P.ng_ev) {
+    if (P.gs) LSH_HIP(hipStreamSynchronize(P.gs));  // (this level's Gram rows, read from the previous temporaries)
+  } else if (P.ng_level == l) {
+    LSH_HIP(hipStreamWaitEvent(s, P.ng_ev, 0));
+  }
+  if (!lv.host_ready) {
+    if (l == P.L) {
+      lv.cand = P.leaf_pts_h;
+      lv.m = (int)lv.cand.size();
+    } else {
+      level_candidates(P, l, lv);
     }
   }
+  const std::vector<I2> ring = proxy_ring(lv.sx, lv.sy, d.proxy_width);
+  if (!P.interp_wait)
+    P.sid.reset(0);  // (the previous level's temporaries are no longer in use)
+  else if (l > d.full_levels)
+    P.place_level(l, level_scratch_bytes(d, lv.m, (long)ring.size(), (long)ring.size() * (P.hbs_order > 4 ? 2 : 1)));
+  level_id(P, l, lv, ring, s, later);
+  if (!lv.skel_known) skeleton_known(P, l);
+  if (!later || later->m == 0) plan_id_finish(P, l, s);
+}
+
+// rh: host memory of the upload, until the work on s is done
+void plan_id_later(lsh_plan_s& P, int l, const BpInterp& I, std::vector<int>& rh, hipStream_t s) {
+  Level& lv = P.lev[l];
+  lv.U64.alloc(sizeof(z64) * (size_t)lv.m * lv.k);
+  bp_interp(s, I, lv.J.data(), rh, lv.U64.as<z64>());
+  plan_id_finish(P, l, s);
 }
 
 // Low-rank form of parent level l's sibling block for the Woodbury merge:
@@ -746,6 +804,28 @@ size_t rowid_scratch_bytes(long m, double tol) {
   return z.total + std::max({q.total, mem::round_up(rowid_gram_ws((int)m)), mem::round_up(rowid_bp_ws((int)m))});
 }
 
+// temporaries of one level's row ID: m candidates, np ring points, ncols
+// columns of the proxy matrix
+size_t level_scratch_bytes(const lsh_desc& d, long m, long np, long ncols) {
+  mem::Sizer t;
+  t.add_n<I2>(m);
+  t.add_n<I2>(np);
+  if (d.tol > 0) t.add_n<z64>((size_t)m * ncols);
+  return t.total + rowid_scratch_bytes(m, d.tol);
+}
+
+// temporaries of a sibling block of order c and its low-rank form
+size_t sibling_scratch_bytes(const lsh_desc& d, long c) {
+  mem::Sizer t;
+  t.add_n<I2>(c);
+  t.add_n<I2>(c);
+  if (d.merge == LSH_MERGE_SCHUR || (d.merge == LSH_MERGE_AUTO && d.tol == 0)) return t.total;
+  t.add_n<z64>((size_t)c * c);  // copy of G_ab (overwritten by the row ID)
+  t.add_n<I2>(c);
+  t.add_n<I2>(c);
+  return t.total + rowid_scratch_bytes(c, d.tol);
+}
+
 // Plan sizes (bounds) and the factor's rank profile under the same bounds.
 PlanBytes plan_bytes(const lsh_desc& d, Profile* prof) {
   int p = d.n / d.leaf, lg = 0;
@@ -787,11 +867,7 @@ PlanBytes plan_bytes(const lsh_desc& d, Profile* prof) {
       z.add_n<int>(kb);
     }
     const long ncols = (horder > 4 ? 2 : 1) * np[l];
-    mem::Sizer t;
-    t.add_n<I2>(m[l]);
-    t.add_n<I2>(np[l]);
-    if (d.tol > 0) t.add_n<z64>((size_t)m[l] * ncols);
-    sid = std::max(sid, t.total + rowid_scratch_bytes(m[l], d.tol));
+    sid = std::max(sid, level_scratch_bytes(d, m[l], np[l], ncols));
     // the parent's Gram rows, built during this row ID (level_id)
     if (d.tol >= 1e-7 && !d.plan_cache && l >= 2 && l - 1 > d.full_levels && m[l] >= kNextGramMin) {
       const long pcols = (horder > 4 ? 2 : 1) * np[l - 1];
@@ -808,21 +884,13 @@ PlanBytes plan_bytes(const lsh_desc& d, Profile* prof) {
     z.add_n<z64>(cc);
     z.add_n<z64>(cc);
     if (f32) { z.add(e * cc); z.add(e * cc); }
-    mem::Sizer t;
-    t.add_n<I2>(c);
-    t.add_n<I2>(c);
     if (lowrank) {
       z.add_n<z64>(cc);                     // U of the sibling block's row ID
       z.add_n<z64>(2 * cr);                 // [L; R]
       z.add_n<z64>(2 * cr);                 // [L^T; R^T]
       if (f32) { z.add(e * 2 * cr); z.add(e * 2 * cr); }
-      t.add_n<z64>(cc);                     // copy of G_ab (overwritten by the row ID)
-      t.add_n<I2>(c);
-      t.add_n<I2>(c);
-      ssib = std::max(ssib, t.total + rowid_scratch_bytes((long)c, d.tol));
-    } else {
-      ssib = std::max(ssib, t.total);
     }
+    ssib = std::max(ssib, sibling_scratch_bytes(d, (long)c));
   }
   z.add(ConvOperator::bytes(d.n));
   b.persist = z.total;
@@ -2726,6 +2794,8 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
     ~BsGuard() {  // (the side stream's rows read plan memory: drained before the streams go back)
       if (b->pg) (void)hipStreamSynchronize(b->pg);
       P->gs = nullptr;
+      P->ng_ev = nullptr;
+      P->interp_wait = nullptr;
       P->skel_cb = nullptr;  // (it refers to this call's thread state)
       BuildStreams::release(b);
     }
@@ -2736,7 +2806,7 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
   mem::Bind bind(&P->persist);  // (plan_init; each plan thread binds its own)
   plan_init(*P, ps);
   const int L = P->L;
-  bs->events(2 * L + 5);  // [l]: U_l ready, [L+1+l]: G_l ready, [2L+2]: done
+  bs->events(2 * L + 6);  // [l]: U_l ready, [L+1+l]: G_l ready, [2L+2]: done, [2L+5]: parent Gram rows
   std::vector<hipEvent_t>& ev = bs->ev;
   if (fsm) {  // the factor stream follows the copy of b on the caller's stream
     LSH_HIP(hipEventRecord(ev[2 * L + 3], s));
@@ -2745,7 +2815,7 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
   std::mutex mu;
   std::condition_variable cv;
   int doneU = L + 1;  // lowest level with U_l ready
-  int running = 2;                   // plan threads still running
+  int running = 3;                   // plan threads still running
   bool finished = false, failed = false;
   std::exception_ptr err;
   auto fail = [&] {
@@ -2811,6 +2881,25 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
     cv.notify_all();
     return true;
   };
+  // A level's interpolation matrix is not needed for the next level's row ID,
+  // only its skeleton is: a third thread forms it on the side stream of the
+  // parent Gram rows (no more streams than hardware queues), and the level's
+  // temporaries are free again (interpDone) for the row ID two levels on.
+  const bool defer = block_pivots(*P) && !desc->plan_cache;
+  if (defer) P->ng_ev = ev[2 * L + 5];
+  struct Interp {
+    int l;
+    BpInterp I;
+  };
+  std::deque<Interp> interps;
+  bool idsDone = false;
+  int interpDone = L + 1;  // lowest level whose temporaries are free
+  auto wait_interp = [&](int l) {  // false if the plan failed
+    std::unique_lock<std::mutex> g(mu);
+    cv.wait(g, [&] { return failed || interpDone <= l; });
+    return !failed;
+  };
+  if (defer) P->interp_wait = wait_interp;
   const char* ess = std::getenv("LSH_SIB_SYNC");
   const bool sib_sync = !(ess && *ess == '0');
   std::thread th([&] {
@@ -2818,17 +2907,44 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
       LSH_HIP(hipSetDevice(dev));
       mem::Bind tbind(&P->persist);
       for (int l = L; l >= 1; --l) {
-        plan_id(*P, l, ps);
-        LSH_HIP(hipEventRecord(ev[l], ps));
-        { std::lock_guard<std::mutex> g(mu); doneU = l; }
+        BpInterp I;
+        plan_id(*P, l, ps, defer ? &I : nullptr);
+        const bool later = defer && I.m > 0;
+        if (!later) LSH_HIP(hipEventRecord(ev[l], ps));
+        {
+          std::lock_guard<std::mutex> g(mu);
+          interps.push_back(Interp{l, I});  // (in level order, also those that are complete)
+        }
         cv.notify_all();
       }
-      // the remaining sibling blocks (in the row IDs' temporaries: every row
-      // ID is done; the parent Gram rows too), then the operator spectrum
+      {
+        std::lock_guard<std::mutex> g(mu);
+        idsDone = true;
+      }
+      cv.notify_all();
+      // the remaining sibling blocks (in the row IDs' temporaries: in deferred
+      // builds the part below the last row ID's if it is large enough, else
+      // once its interpolation matrix is formed; the parent Gram rows have been
+      // waited for), then the operator spectrum
       LSH_HIP(hipStreamSynchronize(ps));
-      LSH_HIP(hipStreamSynchronize(P->gs));
-      for (int l = claim(); l >= 0; l = claim())
-        if (!sibling(l, ps, P->sid, false)) break;
+      if (!defer) LSH_HIP(hipStreamSynchronize(P->gs));
+      mem::Arena part;
+      for (int l = claim(); l >= 0; l = claim()) {
+        mem::Arena* tmp = &P->sid;
+        if (defer) {
+          const size_t room = (P->sid.cap() - P->id_need[1]) / mem::kGranule * mem::kGranule;
+          const int first = desc->full_levels + 1;
+          if (room >= sibling_scratch_bytes(*desc, P->lev[l + 1].k)) {
+            if (first + 1 <= L && !wait_interp(first + 1)) break;
+            part.attach(P->sid.base(), room, "plan row-ID temporaries");
+            tmp = &part;
+          } else if (!wait_interp(first)) {
+            break;
+          }
+        }
+        if (!sibling(l, ps, *tmp, false)) break;
+      }
+      if (defer) (void)wait_interp(desc->full_levels + 1);
       plan_finish(*P, ps);
       LSH_HIP(hipEventRecord(ev[2 * L + 2], ps));
     } catch (...) {
@@ -2844,6 +2960,36 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
         if (!sibling(l, ps2, P->ssib, sib_sync)) break;
     } catch (...) {
       fail();
+    }
+    leave();
+  });
+  std::thread th3([&] {
+    try {
+      LSH_HIP(hipSetDevice(dev));
+      mem::Bind tbind(&P->persist);
+      std::vector<int> rh;
+      for (;;) {
+        Interp t;
+        {
+          std::unique_lock<std::mutex> g(mu);
+          cv.wait(g, [&] { return failed || idsDone || !interps.empty(); });
+          if (failed || interps.empty()) break;
+          t = interps.front();
+          interps.pop_front();
+        }
+        if (t.I.m > 0) {
+          plan_id_later(*P, t.l, t.I, rh, P->gs);
+          LSH_HIP(hipEventRecord(ev[t.l], P->gs));
+        }
+        { std::lock_guard<std::mutex> g(mu); doneU = t.l; }
+        cv.notify_all();
+        if (t.I.m > 0) LSH_HIP(hipEventSynchronize(ev[t.l]));
+        { std::lock_guard<std::mutex> g(mu); interpDone = t.l; }
+        cv.notify_all();
+      }
+    } catch (...) {
+      fail();
+      cv.notify_all();
     }
     leave();
   });
@@ -2898,6 +3044,7 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
   }
   th.join();
   th2.join();
+  th3.join();
   if (err) std::rethrow_exception(err);
   if (ferr) std::rethrow_exception(ferr);
   LSH_HIP(hipStreamWaitEvent(s, ev[2 * L + 2], 0));

@@ -1,0 +1,77 @@
+"""lsh_build, whose levels' interpolation matrices are formed beside the next
+level's row ID: the same factor bit for bit as lsh_plan_create +
+lsh_factor_create over depths, uncompressed top levels, pivoting rules and
+precisions, and for builds that run at the same time on two threads."""
+import threading
+
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def cuda(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+CASES = [(8, 4, 4, 1e-4, 0, "fp32"), (16, 4, 4, 1e-5, 0, "fp64"), (40, 5, 6, 1e-4, 1, "fp32"),
+         (112, 7, 4, 1e-6, 2, "fp64"), (160, 5, 4, 1e-4, 0, "fp32"), (64, 8, 10, 1e-9, 0, "fp64")]
+
+
+@pytest.mark.parametrize("n,leaf,order,tol,fl,prec", CASES)
+@pytest.mark.parametrize("rowid", ["block", "panel"])
+def test_build_equals_separate_calls(n, leaf, order, tol, fl, prec, rowid, monkeypatch):
+    import torch
+    from paper_2007_12718_amd import lsh
+    monkeypatch.setenv("LSH_ROWID", rowid)
+    rng = np.random.default_rng(n)
+    b = cuda(synth.bumps(n, rng))
+    x = cuda(rng.standard_normal((2, n, n)) + 1j * rng.standard_normal((2, n, n)))
+    o = dict(op_order=4, leaf=leaf, tol=tol, proxy_width=3, prec=prec, hbs_order=order, full_levels=fl)
+    P = lsh.Plan(n, 0.5 * n, **o)
+    y = lsh.Factor(P, b).apply_precond(x)
+    for _ in range(2):
+        P2, F2 = lsh.build(n, 0.5 * n, b, **o)
+        assert P2.ranks() == P.ranks() and P2.lowrank_ranks() == P.lowrank_ranks()
+        assert torch.equal(F2.apply_precond(x), y)
+
+
+def test_builds_on_two_threads():
+    import torch
+    from paper_2007_12718_amd import lsh
+    out, ref, err = {}, {}, []
+
+    def one(i, n, leaf, prec):
+        try:
+            st = torch.cuda.Stream()
+            with torch.cuda.stream(st):
+                rng = np.random.default_rng(i)
+                b = cuda(synth.bumps(n, rng))
+                x = cuda(rng.standard_normal((1, n, n)) + 0j)
+                res = []
+                for _ in range(3):
+                    P, F = lsh.build(n, 0.5 * n, b, op_order=4, leaf=leaf, tol=1e-4, proxy_width=2, prec=prec)
+                    res.append(F.apply_precond(x))
+                    st.synchronize()
+                    F.close()
+                    P.close()
+                out[i] = res
+        except Exception as e:  # (reported by the main thread)
+            err.append(e)
+
+    todo = [(0, 96, 6, "fp32"), (1, 128, 8, "fp64")]
+    for t in todo:
+        one(*t)
+    ref.update({i: v[0] for i, v in out.items()})
+    out.clear()
+    ths = [threading.Thread(target=one, args=t) for t in todo]
+    for t in ths:
+        t.start()
+    for t in ths:
+        t.join()
+    assert not err, err
+    for i, v in out.items():
+        assert all(torch.equal(y, ref[i]) for y in v)
