@@ -62,15 +62,91 @@ struct GemmP {
   int nsplit = 1, kchunk = 0;
 };
 
+// One operand's way from memory into its LDS planes: ROWS x BK elements per K
+// tile, E of them per thread, the lanes along whichever of the two indices is
+// contiguous in memory.  In both orders a thread's loads are one pointer plus
+// multiples of a uniform step, and so are its LDS stores, so the order is
+// settled once before the K loop; a tile that lies inside the matrix is read
+// without a bound, one on its edge reads the matrix's first element instead of
+// what is outside and replaces it by zero on the way to LDS.  (With the order,
+// the bounds and a 64-bit product per element decided inside the K loop the
+// staging was some 25 vector and 10 scalar instructions with four branches per
+// element, and took a quarter of the FP64 product's time.)
+template <typename R, int ROWS, int BK, int LD>
+struct GemmStage {
+  static constexpr int E = ROWS * BK / 256;
+  const cplx<R>*X, *p;
+  long step, kstep;
+  int q, qs, ql, qk, w, wl, wk;  // load e is inside when q + e qs < ql and w < wl
+  int at, ts;
+  R sg;
+  bool rows_in;
+  // rows r0 .. r0 + ROWS - 1 of nrows; kfast: consecutive k are adjacent in memory
+  __device__ __forceinline__ void init(const cplx<R>* X_, long ld, bool kfast, bool conj, int r0, int nrows, int K,
+                                       int tid) {
+    X = X_;
+    sg = conj ? R(-1) : R(1);
+    rows_in = r0 + ROWS <= nrows;
+    const int row = kfast ? tid / BK : tid % ROWS, k = kfast ? tid % BK : tid / ROWS;
+    p = X + (kfast ? (long)(r0 + row) * ld + k : (long)k * ld + r0 + row);
+    step = (kfast ? 256 / BK : 256 / ROWS) * ld;
+    kstep = kfast ? BK : BK * ld;
+    q = kfast ? r0 + row : k;
+    qs = kfast ? 256 / BK : 256 / ROWS;
+    ql = kfast ? nrows : K;
+    qk = kfast ? 0 : BK;
+    w = kfast ? k : r0 + row;
+    wl = kfast ? K : nrows;
+    wk = kfast ? BK : 0;
+    at = row * LD + k;
+    ts = kfast ? (256 / BK) * LD : 256 / ROWS;
+  }
+  __device__ __forceinline__ void load(cplx<R> (&v)[E], bool k_in) const {
+    if (rows_in && k_in) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[e] = p[e * step];
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[e] = *(q + e * qs < ql && w < wl ? p + e * step : X);
+    }
+  }
+  // what the last load fetched; then on to the next K tile
+  __device__ __forceinline__ void store(const cplx<R> (&v)[E], bool k_in, R* re, R* im) {
+    if (rows_in && k_in) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        re[at + e * ts] = v[e].x;
+        im[at + e * ts] = sg * v[e].y;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const bool in = q + e * qs < ql && w < wl;
+        re[at + e * ts] = in ? v[e].x : R(0);
+        im[at + e * ts] = in ? sg * v[e].y : R(0);
+      }
+    }
+    p += kstep;
+    q += qk;
+    w += wk;
+  }
+};
+
 // Tile: 2 x 2 wavefronts, each owning WM x WN blocks of 16 x 16 outputs, so the
 // workgroup tile is (32 WM) x (32 WN); K advances GBK (16 or 32) at a time.  LDS holds
 // separate real / imaginary planes laid out [row][k] with stride 17, which
 // keeps both the coalesced global->LDS stores and the MFMA operand reads
 // (16 rows x 4 k per instruction) within one extra bank conflict.  The next
 // K tile is prefetched into registers while the current one is multiplied.
+// Two wavefronts per SIMD are asked for so that the accumulators stay in
+// ordinary registers: with one, the compiler keeps them in both halves of the
+// register file and moves every one across inside the K loop (128 moves to 128
+// matrix instructions; the bare instruction then reaches 50 TF/s of the 78
+// that it does otherwise).  4096^3: 54 TF/s with the moves and the former
+// staging, 59 without the moves, 68 with GemmStage as well.
 
 template <typename R, int WM, int WN, int GBK = 16>
-__global__ __launch_bounds__(256) void k_cgemm(GemmP<R> P) {
+__global__ __launch_bounds__(256, 2) void k_cgemm(GemmP<R> P) {
   constexpr int GLD = GBK + 1;
   using M4 = Mfma<R>;
   using acc_t = typename M4::acc_t;
@@ -106,57 +182,24 @@ __global__ __launch_bounds__(256) void k_cgemm(GemmP<R> P) {
     for (int j = 0; j < WN; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) { cr[i][j][r] = 0; ci[i][j][r] = 0; }
+  GemmStage<R, BM, GBK, GLD> ga;
+  GemmStage<R, BN, GBK, GLD> gb;
+  ga.init(A, P.lda, aN, aC, m0, P.M, P.K, tid);
+  gb.init(B, P.ldb, !bN, bC, n0, P.N, P.K, tid);
   cplx<R> ra[EA], rb[EB];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int e = 0; e < EA; ++e) {
-      const int idx = tid + e * 256;
-      int m, k;
-      if (aN) { m = idx / GBK; k = idx % GBK; }
-      else { k = idx / BM; m = idx % BM; }
-      const int gm = m0 + m, gk = k0 + k;
-      cplx<R> v = mk<R>(0, 0);
-      if (gm < P.M && gk < P.K) v = aN ? A[(long)gm * P.lda + gk] : A[(long)gk * P.lda + gm];
-      ra[e] = v;
-    }
-#pragma unroll
-    for (int e = 0; e < EB; ++e) {
-      const int idx = tid + e * 256;
-      int n, k;
-      if (bN) { k = idx / BN; n = idx % BN; }
-      else { n = idx / GBK; k = idx % GBK; }
-      const int gn = n0 + n, gk = k0 + k;
-      cplx<R> v = mk<R>(0, 0);
-      if (gn < P.N && gk < P.K) v = bN ? B[(long)gk * P.ldb + gn] : B[(long)gn * P.ldb + gk];
-      rb[e] = v;
-    }
-  };
-  auto store = [&]() {
-#pragma unroll
-    for (int e = 0; e < EA; ++e) {
-      const int idx = tid + e * 256;
-      int m, k;
-      if (aN) { m = idx / GBK; k = idx % GBK; }
-      else { k = idx / BM; m = idx % BM; }
-      sAr[m][k] = ra[e].x;
-      sAi[m][k] = aC ? -ra[e].y : ra[e].y;
-    }
-#pragma unroll
-    for (int e = 0; e < EB; ++e) {
-      const int idx = tid + e * 256;
-      int n, k;
-      if (bN) { k = idx / BN; n = idx % BN; }
-      else { n = idx / GBK; k = idx % GBK; }
-      sBr[n][k] = rb[e].x;
-      sBi[n][k] = bC ? -rb[e].y : rb[e].y;
-    }
-  };
-  load(0);
-  store();
+  if (P.K > 0) {
+    ga.load(ra, GBK <= P.K);
+    gb.load(rb, GBK <= P.K);
+    ga.store(ra, GBK <= P.K, &sAr[0][0], &sAi[0][0]);
+    gb.store(rb, GBK <= P.K, &sBr[0][0], &sBi[0][0]);
+  }
   __syncthreads();
   for (int k0 = 0; k0 < P.K; k0 += GBK) {
-    const bool more = k0 + GBK < P.K;
-    if (more) load(k0 + GBK);
+    const bool more = k0 + GBK < P.K, k_in = k0 + 2 * GBK <= P.K;  // (of the next K tile)
+    if (more) {
+      ga.load(ra, k_in);
+      gb.load(rb, k_in);
+    }
 #pragma unroll
     for (int kk = 0; kk < GBK / 4; ++kk) {
       const int k = kk * 4 + (lane >> 4);
@@ -183,7 +226,8 @@ __global__ __launch_bounds__(256) void k_cgemm(GemmP<R> P) {
     }
     __syncthreads();
     if (more) {
-      store();
+      ga.store(ra, k_in, &sAr[0][0], &sAi[0][0]);
+      gb.store(rb, k_in, &sBr[0][0], &sBi[0][0]);
       __syncthreads();
     }
   }
@@ -218,7 +262,11 @@ __global__ __launch_bounds__(256) void k_cgemm(GemmP<R> P) {
 // 32g .. 32g+31) takes k = 16g + s at step s: each lane then reads its
 // operands for four steps with one 16-byte LDS load per plane.  Row stride
 // BK + 4 floats keeps those loads free of bank conflicts.  Every tile shape
-// and depth issues the same instructions per output in the same order.
+// and depth issues the same instructions per output in the same order.  The
+// 32-deep 64 x 64 tile is held to three wavefronts per SIMD (154 registers;
+// left to itself the compiler takes 170, which is two).  4096^3, 8 M N K
+// operations counted: 120 TF/s with 64 x 64 and 119 with 128 x 64 tiles before
+// GemmStage, 160 and 168 with it; 1024 products of order 64: 72 and 85.
 // Accumulator register r of lane l holds D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
 constexpr int X32_BK = 32;  // K depth of the split-K chunks' tiles
 
@@ -248,57 +296,24 @@ __device__ __forceinline__ void cgemm_x32_tile(const GemmP<float>& P, long b, in
     for (int j = 0; j < WN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) { t1[i][j][r] = 0; t2[i][j][r] = 0; t3[i][j][r] = 0; }
+  GemmStage<float, BM, BK, LDK> ga;
+  GemmStage<float, BN, BK, LDK> gb;
+  ga.init(A, P.lda, aN, aC, m0, P.M, P.K, tid);
+  gb.init(B, P.ldb, !bN, bC, n0, P.N, P.K, tid);
   cplx<float> ra[EA], rb[EB];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int e = 0; e < EA; ++e) {
-      const int idx = tid + e * 256;
-      int m, k;
-      if (aN) { m = idx / BK; k = idx % BK; }
-      else { k = idx / BM; m = idx % BM; }
-      const int gm = m0 + m, gk = k0 + k;
-      cplx<float> v = mk<float>(0, 0);
-      if (gm < P.M && gk < P.K) v = aN ? A[(long)gm * P.lda + gk] : A[(long)gk * P.lda + gm];
-      ra[e] = v;
-    }
-#pragma unroll
-    for (int e = 0; e < EB; ++e) {
-      const int idx = tid + e * 256;
-      int n, k;
-      if (bN) { k = idx / BN; n = idx % BN; }
-      else { n = idx / BK; k = idx % BK; }
-      const int gn = n0 + n, gk = k0 + k;
-      cplx<float> v = mk<float>(0, 0);
-      if (gn < P.N && gk < P.K) v = bN ? B[(long)gk * P.ldb + gn] : B[(long)gn * P.ldb + gk];
-      rb[e] = v;
-    }
-  };
-  auto store = [&]() {
-#pragma unroll
-    for (int e = 0; e < EA; ++e) {
-      const int idx = tid + e * 256;
-      int m, k;
-      if (aN) { m = idx / BK; k = idx % BK; }
-      else { k = idx / BM; m = idx % BM; }
-      sAr[m][k] = ra[e].x;
-      sAi[m][k] = aC ? -ra[e].y : ra[e].y;
-    }
-#pragma unroll
-    for (int e = 0; e < EB; ++e) {
-      const int idx = tid + e * 256;
-      int n, k;
-      if (bN) { k = idx / BN; n = idx % BN; }
-      else { n = idx / BK; k = idx % BK; }
-      sBr[n][k] = rb[e].x;
-      sBi[n][k] = bC ? -rb[e].y : rb[e].y;
-    }
-  };
-  load(0);
-  store();
+  if (P.K > 0) {
+    ga.load(ra, BK <= P.K);
+    gb.load(rb, BK <= P.K);
+    ga.store(ra, BK <= P.K, &sAr[0][0], &sAi[0][0]);
+    gb.store(rb, BK <= P.K, &sBr[0][0], &sBi[0][0]);
+  }
   __syncthreads();
   for (int k0 = 0; k0 < P.K; k0 += BK) {
-    const bool more = k0 + BK < P.K;
-    if (more) load(k0 + BK);
+    const bool more = k0 + BK < P.K, k_in = k0 + 2 * BK <= P.K;  // (of the next K tile)
+    if (more) {
+      ga.load(ra, k_in);
+      gb.load(rb, k_in);
+    }
 #pragma unroll
     for (int h = 0; h < BK / 8; ++h) {  // groups of four k steps
       f4v ar[WM], ai[WM], as[WM], br[WN], bi[WN], bs[WN];
@@ -332,7 +347,8 @@ __device__ __forceinline__ void cgemm_x32_tile(const GemmP<float>& P, long b, in
     }
     __syncthreads();
     if (more) {
-      store();
+      ga.store(ra, k_in, &sAr[0][0], &sAi[0][0]);
+      gb.store(rb, k_in, &sBr[0][0], &sBi[0][0]);
       __syncthreads();
     }
   }
@@ -358,7 +374,7 @@ __device__ __forceinline__ void cgemm_x32_tile(const GemmP<float>& P, long b, in
 }
 
 template <int WM, int WN, int BK>
-__global__ __launch_bounds__(256, (WM * WN >= 4 ? 1 : 2)) void k_cgemm_x32(GemmP<float> P) {
+__global__ __launch_bounds__(256, (WM * WN >= 4 ? 1 : WM * WN * BK == 32 ? 3 : 2)) void k_cgemm_x32(GemmP<float> P) {
   constexpr int BM = 64 * WM, BN = 64 * WN;
   if (P.skip && *P.skip) return;  // uniform across the launch
   // XCD-aware tile order (see k_cgemm)
@@ -376,7 +392,7 @@ __global__ __launch_bounds__(256, (WM * WN >= 4 ? 1 : 2)) void k_cgemm_x32(GemmP
 // Split K (64 x 64 tiles, XCD-aware order as above): grid z runs over
 // (problem, K chunk); chunk ks of problem b writes its partial product to
 // part + (b nsplit + ks) M N.
-__global__ __launch_bounds__(256, 2) void k_cgemm_x32_splitk(GemmP<float> P) {
+__global__ __launch_bounds__(256, 3) void k_cgemm_x32_splitk(GemmP<float> P) {
   const long T = (long)gridDim.x * gridDim.y * gridDim.z;
   long L = blockIdx.x + (long)gridDim.x * (blockIdx.y + (long)gridDim.y * blockIdx.z);
   const long T8 = (T / 8) * 8;
@@ -427,7 +443,7 @@ struct GemmGroupDev {
   long tile0;
 };
 
-__global__ __launch_bounds__(256, 4) void k_cgemm_x32_grouped(const GemmGroupDev* G, int ng) {
+__global__ __launch_bounds__(256, 3) void k_cgemm_x32_grouped(const GemmGroupDev* G, int ng) {
   const long L = blockIdx.x + (long)gridDim.x * blockIdx.y;
   int lo = 0, hi = ng - 1;  // last group with tile0 <= L
   while (lo < hi) {
@@ -509,11 +525,13 @@ const char* gemm_variant_name(int prec, int v) {
 // Without a tuned entry: a wave-quantisation model for FP32 (a launch takes
 // ceil(tiles / (256 CUs x resident workgroups per CU)) rounds, and a full
 // round costs (resident workgroups x tile area) / (per-CU efficiency of that
-// tile)), and the 32-deep 64 x 64 tile for FP64 (47-50 TF/s alone on the
-// plan's Gram and interpolation shapes, against 45-48 with 16-deep and 23-42
-// with 128 x 64 tiles).
+// tile)), from rates of 168 TF/s for the 128 x 64 tile and 160 for 64 x 64 at
+// 4096^3, 120 against 97 for 256 products of order 128, 50 against 85 for 1024
+// of order 64.  For FP64 the 32-deep 64 x 64 tile: 68 TF/s at 4096^3 with
+// either depth, 51 against 48 at 1280^3, 44 against 50 for 1024 products of
+// order 64; 61 and 37 with 128 x 64 tiles.
 struct TileModel { int variant, bm, bn, resident; double eff; };
-static const TileModel kF32Model[2] = {{1, 128, 64, 2, 0.60}, {0, 64, 64, 4, 0.69}};
+static const TileModel kF32Model[2] = {{1, 128, 64, 2, 1.00}, {0, 64, 64, 3, 0.95}};
 
 static int model_variant(int prec, int M, int N, int batch) {
   if (prec != 1) return 2;

@@ -1081,10 +1081,11 @@ __global__ __launch_bounds__(64 * BP_CW) void k_bp_chol(const z64* M, const z64*
 // rows per workgroup: four waves of 16 JT rows.  The MFMA work of a
 // workgroup, not the memory, bounds a launch here (FP64 16x16x4 at 64 cycles
 // a wave), and early steps have few depth chunks: small row blocks (JT = 1)
-// keep every unit busy then.
+// keep every unit busy then.  (Two wavefronts per SIMD asked for: see k_cgemm;
+// six matrix instructions stood beside 96 accumulator moves before.)
 constexpr int BP_WT_JT = 1, BP_WT_ROWS = 64 * BP_WT_JT;
 template <int BP_KC>
-__global__ __launch_bounds__(256) void k_bp_wt(const z64* Lt, const int* J, int m, const int* st, z64* part) {
+__global__ __launch_bounds__(256, 2) void k_bp_wt(const z64* Lt, const int* J, int m, const int* st, z64* part) {
   typedef double d4 __attribute__((ext_vector_type(4)));
   __shared__ double Apr[BP_NP][BP_KC + 1], Api[BP_NP][BP_KC + 1];
   if (st[BPS_DONE]) return;
