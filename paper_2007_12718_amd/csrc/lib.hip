@@ -1950,19 +1950,13 @@ void fgmres_one(lsh_factor_s& F, SolveWs& W, const z64* f, z64* x, const lsh_sol
     clk.mark(1, s);
     P.op.apply(s, F.b.as<double>(), zj, w, 1, transposed);
     clk.mark(2, s);
-    // classical Gram-Schmidt, twice
-    multidot(s, V, N, j + 1, w, N, h1, part);
-    multiaxpy(s, w, V, N, j + 1, h1, N);
-    multidot(s, V, N, j + 1, w, N, h2, part);
-    multiaxpy(s, w, V, N, j + 1, h2, N);
-    multidot(s, w, 0, 1, w, N, h2 + (j + 1), part);
+    cgs2(s, V, N, j + 1, w, N, 1, 1u, h1, h2, maxit + 2, part);
     clk.mark(3, s);
     LSH_HIP(hipMemcpyAsync(hv.data(), h1, sizeof(z64) * (j + 1), hipMemcpyDeviceToHost, s));
     LSH_HIP(hipMemcpyAsync(hv2.data(), h2, sizeof(z64) * (j + 2), hipMemcpyDeviceToHost, s));
     LSH_HIP(hipStreamSynchronize(s));
     clk.add();
     const double hn = std::sqrt(hv2[j + 1].x);
-    if (hn > 0) scale_by_invnorm(s, w, w, h2 + (j + 1), N);
     auto Hc = [&](int r, int c) -> std::complex<double>& { return H[(size_t)r * maxit + c]; };
     for (int i = 0; i <= j; ++i) Hc(i, j) = {hv[i].x + hv2[i].x, hv[i].y + hv2[i].y};
     Hc(j + 1, j) = hn;
@@ -2071,16 +2065,9 @@ void fgmres_multi(lsh_factor_s& F, SolveWs& W, const z64* f, z64* x, int nr, con
     clk.mark(1, s);
     P.op.apply(s, F.b.as<double>(), zj, wj, nr, transposed);
     clk.mark(2, s);
-    for (int r = 0; r < nr; ++r) {
-      if (!run[r].active) continue;
-      z64* w = wj + r * N;
-      z64 *a1 = h1 + r * hs, *a2 = h2 + r * hs;
-      multidot(s, V + r * N, S, j + 1, w, N, a1, part);
-      multiaxpy(s, w, V + r * N, S, j + 1, a1, N);
-      multidot(s, V + r * N, S, j + 1, w, N, a2, part);
-      multiaxpy(s, w, V + r * N, S, j + 1, a2, N);
-      multidot(s, w, 0, 1, w, N, a2 + (j + 1), part);
-    }
+    unsigned active = 0;
+    for (int r = 0; r < nr; ++r) active |= run[r].active ? 1u << r : 0u;
+    cgs2(s, V, S, j + 1, wj, N, nr, active, h1, h2, hs, part);
     clk.mark(3, s);
     LSH_HIP(hipMemcpyAsync(hv.data(), h1, sizeof(z64) * nr * hs, hipMemcpyDeviceToHost, s));
     LSH_HIP(hipMemcpyAsync(hv2.data(), h2, sizeof(z64) * nr * hs, hipMemcpyDeviceToHost, s));
@@ -2091,9 +2078,7 @@ void fgmres_multi(lsh_factor_s& F, SolveWs& W, const z64* f, z64* x, int nr, con
       if (!R.active) continue;
       const z64* e1 = hv.data() + (size_t)r * hs;
       const z64* e2 = hv2.data() + (size_t)r * hs;
-      z64* w = wj + r * N;
       const double hn = std::sqrt(e2[j + 1].x);
-      if (hn > 0) scale_by_invnorm(s, w, w, h2 + r * hs + (j + 1), N);
       auto Hc = [&](int i, int c) -> cd& { return R.H[(size_t)i * maxit + c]; };
       for (int i = 0; i <= j; ++i) Hc(i, j) = {e1[i].x + e2[i].x, e1[i].y + e2[i].y};
       Hc(j + 1, j) = hn;
@@ -2116,7 +2101,7 @@ void fgmres_multi(lsh_factor_s& F, SolveWs& W, const z64* f, z64* x, int nr, con
       if (R.est < o.tol || hn == 0) {
         R.active = false;
         --nact;
-        fill_zero(s, w, sizeof(z64) * N);  // keeps this vector's later applies at zero
+        fill_zero(s, wj + r * N, sizeof(z64) * N);  // keeps this vector's later applies at zero
       }
     }
   }

@@ -1,8 +1,10 @@
 // Kernel-entry generator and FGMRES vector kernels.  All FP64.
+#include <algorithm>
 #include <cmath>
 
 #include "ops.hpp"
 #include "prof.hpp"
+#include "wave.hpp"
 
 namespace lsh {
 
@@ -109,17 +111,123 @@ void multidot(hipStream_t s, const z64* V, long ldv, int nv, const z64* w, long 
   LSH_LAUNCH_CHECK();
 }
 
-__global__ void k_multiaxpy(z64* w, const z64* __restrict__ V, long ldv, int nv, const z64* __restrict__ h, long N) {
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < N; i += (long)gridDim.x * blockDim.x) {
-    z64 a = w[i];
-    for (int v = 0; v < nv; ++v) a = a - V[v * ldv + i] * h[v];
-    w[i] = a;
+// One FGMRES step's classical Gram-Schmidt, twice, and the scaling of the new
+// basis vector, for the group's vectors together (blockIdx.y), in four launches:
+//   0  p0 = V^H w, one partial sum per workgroup
+//   1  h1 = sum p0;  w -= V h1;  p1 = V^H w
+//   2  h2 = sum p1;  w -= V h2;  p2 = |w|^2
+//   3  |w|^2 = sum p2;  w /= |w| (left alone where that is not positive)
+// Every workgroup adds up the partial sums it needs by itself, which costs
+// less than a launch for them, and step 1's second look at its part of V finds
+// it in L2.  About 256 workgroups in all share the group, one per compute
+// unit, so there are few partial sums.  Bound by the three passes over V (8
+// vectors of 512 x 512 against 6 each: 22 + 36 + 22 + 8 us, V from the memory
+// side's cache at up to 10 TB/s) and on small grids by the launches.  With
+// nine launches for each vector by itself this took some 320 us, and the solve
+// of 8 fields on 512 x 512 14.8 ms against 13.9.
+constexpr int CGS_NT = 1024, CGS_E = 4, CGS_WG = 256;
+
+template <int STEP>
+__global__ __launch_bounds__(CGS_NT) void k_cgs(const z64* __restrict__ V, long ldv, int nv, z64* w, long N,
+                                                unsigned active, const z64* __restrict__ pin, z64* __restrict__ pout,
+                                                z64* h, int hs) {
+  __shared__ z64 red[STEP <= 1 ? MD_MAXV : 1][CGS_NT / 64];
+  __shared__ z64 hv[STEP == 0 ? 1 : MD_MAXV];
+  const int r = blockIdx.y, nb = gridDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (!((active >> r) & 1u)) return;
+  V += r * N;
+  w += r * N;
+  if (STEP > 0) {
+    const int ns = STEP == 3 ? 1 : nv;
+    for (int v = wave; v < ns; v += CGS_NT / 64) {
+      const z64* p = pin + ((long)r * ns + v) * nb;
+      z64 a = mk(0.0, 0.0);
+      for (int k = lane; k < nb; k += 64) a = a + p[k];
+      a = mk(group_sum<64>(a.x), group_sum<64>(a.y));
+      if (lane == 0) {
+        hv[v] = a;
+        if (blockIdx.x == 0) h[(long)r * hs + (STEP == 3 ? nv : v)] = a;
+      }
+    }
+    __syncthreads();
+  }
+  if (STEP == 3) {
+    const double s = hv[0].x > 0 ? 1.0 / sqrt(hv[0].x) : 1.0;
+    for (long i = blockIdx.x * (long)CGS_NT + tid; i < N; i += (long)nb * CGS_NT) w[i] = s * w[i];
+    return;
+  }
+  z64 nrm = mk(0.0, 0.0);
+  bool first = true;
+  for (long i0 = blockIdx.x * (long)(CGS_NT * CGS_E) + tid; i0 - tid < N; i0 += (long)nb * CGS_NT * CGS_E) {
+    // (what lies past the end is read as the last element and counted as zero:
+    // no branch stands between the loads)
+    z64 x[CGS_E];
+    long ix[CGS_E];
+#pragma unroll
+    for (int e = 0; e < CGS_E; ++e) {
+      const long i = i0 + e * CGS_NT;
+      ix[e] = i < N ? i : N - 1;
+      x[e] = w[ix[e]];
+    }
+    if (STEP > 0) {
+#pragma unroll 4
+      for (int v = 0; v < nv; ++v) {
+        const z64* Vv = V + v * ldv;
+        const z64 c = hv[v];
+#pragma unroll
+        for (int e = 0; e < CGS_E; ++e) x[e] = x[e] - Vv[ix[e]] * c;
+      }
+#pragma unroll
+      for (int e = 0; e < CGS_E; ++e)
+        if (i0 + e * CGS_NT < N) w[ix[e]] = x[e];
+    }
+#pragma unroll
+    for (int e = 0; e < CGS_E; ++e)
+      if (i0 + e * CGS_NT >= N) x[e] = mk(0.0, 0.0);
+    if (STEP <= 1) {
+#pragma unroll 4
+      for (int v = 0; v < nv; ++v) {
+        const z64* Vv = V + v * ldv;
+        z64 acc = mk(0.0, 0.0);
+#pragma unroll
+        for (int e = 0; e < CGS_E; ++e) fma_acc(acc, conjg(Vv[ix[e]]), x[e]);
+        acc = mk(group_sum<64>(acc.x), group_sum<64>(acc.y));
+        if (lane == 0) red[v][wave] = first ? acc : red[v][wave] + acc;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < CGS_E; ++e) fma_acc(nrm, conjg(x[e]), x[e]);
+    }
+    first = false;
+  }
+  if (STEP == 2) {
+    nrm = mk(group_sum<64>(nrm.x), group_sum<64>(nrm.y));
+    if (lane == 0) red[0][wave] = nrm;
+  }
+  __syncthreads();
+  const int ns = STEP == 2 ? 1 : nv;
+  for (int v = tid; v < ns; v += CGS_NT) {
+    z64 a = red[v][0];
+    for (int k = 1; k < CGS_NT / 64; ++k) a = a + red[v][k];
+    pout[((long)r * ns + v) * nb + blockIdx.x] = a;
   }
 }
 
-void multiaxpy(hipStream_t s, z64* w, const z64* V, long ldv, int nv, const z64* h, long N) {
-  ProfScope ps("multiaxpy", s, 16.0 * (double)N * (nv + 2));
-  hipLaunchKernelGGL(k_multiaxpy, dim3(2048), dim3(256), 0, s, w, V, ldv, nv, h, N);
+void cgs2(hipStream_t s, const z64* V, long ldv, int nv, z64* w, long N, int nr, unsigned active, z64* h1, z64* h2,
+          int hs, z64* partial) {
+  ProfScope ps("gram_schmidt", s, 16.0 * (double)N * (3 * nv + 7) * __builtin_popcount(active));
+  LSH_REQUIRE(nv <= MD_MAXV && nr >= 1 && nr <= 32, -6, "gram-schmidt: too many vectors");
+  // every workgroup has a piece of the vector: none writes an unset partial sum
+  const int nb = (int)std::max(1L, std::min((long)(CGS_WG / nr), (long)ceil_div(N, (long)(CGS_NT * CGS_E))));
+  z64 *p0 = partial, *p1 = p0 + (size_t)nr * nv * nb, *p2 = p1 + (size_t)nr * nv * nb;  // (at most (2 nv + 1) CGS_WG)
+  const dim3 grid(nb, nr);
+  hipLaunchKernelGGL(k_cgs<0>, grid, dim3(CGS_NT), 0, s, V, ldv, nv, w, N, active, p2, p0, h1, hs);
+  LSH_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_cgs<1>, grid, dim3(CGS_NT), 0, s, V, ldv, nv, w, N, active, p0, p1, h1, hs);
+  LSH_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_cgs<2>, grid, dim3(CGS_NT), 0, s, V, ldv, nv, w, N, active, p1, p2, h2, hs);
+  LSH_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_cgs<3>, grid, dim3(CGS_NT), 0, s, V, ldv, nv, w, N, active, p2, p0, h2, hs);
   LSH_LAUNCH_CHECK();
 }
 

@@ -39,8 +39,13 @@ void add_table_stencil(hipStream_t s, z64* T, int D, double h, const std::vector
 // out[v] = sum_i conj(V[v][i]) w[i], v < nv (V rows at stride ldv)
 void multidot(hipStream_t s, const z64* V, long ldv, int nv, const z64* w, long N, z64* out, z64* partial);
 size_t multidot_partial_bytes(int nv);
-// w -= sum_v V[v] * h[v]
-void multiaxpy(hipStream_t s, z64* w, const z64* V, long ldv, int nv, const z64* h, long N);
+// Classical Gram-Schmidt, twice, of w[r] against V[v][r] (v < nv; rows at
+// stride ldv, right-hand sides at N) for every r < nr whose bit of active is
+// set: the two rounds' coefficients go to h1[r hs + v] and h2[r hs + v],
+// |w[r]|^2 after them to h2[r hs + nv], and w[r] is divided by |w[r]| where
+// that is positive.  partial: multidot_partial_bytes(nv + 1).
+void cgs2(hipStream_t s, const z64* V, long ldv, int nv, z64* w, long N, int nr, unsigned active, z64* h1, z64* h2,
+          int hs, z64* partial);
 // y = x * (1 / sqrt(Re nrm2[0]))
 void scale_by_invnorm(hipStream_t s, z64* y, const z64* x, const z64* nrm2, long N);
 // y = sum_v V[v] * c[v]   (c on device)
