@@ -788,6 +788,144 @@ void mirror_lower(hipStream_t s, cplx<R>* C, int n, long ldc) {
 template void mirror_lower<double>(hipStream_t, cplx<double>*, int, long);
 template void mirror_lower<float>(hipStream_t, cplx<float>*, int, long);
 
+// ------------------------------------------ a few vectors per matrix, FP32
+// Y = alpha A X + beta Z for three vectors per matrix or more, on the 16 x 16 x 4
+// matrix instruction, both operands straight from memory: A's rows and the
+// vectors are both contiguous along K, so lane l reads 16 bytes twice at
+// k = 16 c + 4 (l / 16) of row (or vector) l % 16, which fills whole lines, and
+// the instruction does not care which four k of a chunk its lane groups hold.
+// A workgroup takes 16 rows of one matrix and 16 NT vectors; its KS wavefronts
+// take the 16-deep chunks in turn and their sums meet in LDS in order.  A
+// vector's sums do not depend on how many others there are.  Bound by the bytes
+// of A (or, at the top levels, by a wavefront's chain of chunks).  With a
+// wavefront per row and the vectors' products on the vector unit every row
+// read all the vectors again, and eight vectors of a matrix took two launches:
+// 32 vectors against 1504 rows of 752 took 32 us and take 13; in the solve of 8
+// fields on 512 x 512 these products took 5.3 ms of 13.9 and take 3.0.
+struct SkinnyP {
+  int M0, M1, t0, tiles;  // rows of the two blocks (M1: 0 for one block), tiles of the first and of both
+  int K, nvec;
+  c32 alpha, beta;
+  const c32 *A0, *A1;  // problem b's matrix at A + b sA
+  long lda, sA;
+  const c32 *X0, *X1;  // problem b's vector v at X + b sx + v ldx
+  long sx, ldx;
+  const c32* Z;  // row i of the second block is row M0 + i of Y and Z
+  long sz, ldz;
+  c32* Y;
+  long sy, ldy;
+};
+
+template <int NT, int KS>
+__global__ __launch_bounds__(64 * KS) void k_cskinny(SkinnyP P) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));  // (complex elements: 8-byte aligned)
+  __shared__ float red[KS][NT * 16][33];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r16 = lane & 15, g = lane >> 4;
+  const unsigned b = blockIdx.x / (unsigned)P.tiles;
+  int t = (int)(blockIdx.x - b * (unsigned)P.tiles);
+  const bool second = t >= P.t0;
+  if (second) t -= P.t0;
+  const int M = second ? P.M1 : P.M0, m0 = t * 16, v0 = blockIdx.y * 16 * NT;
+  // rows and vectors past the end repeat the last one; their results are dropped
+  const int row = m0 + r16 < M ? m0 + r16 : M - 1;
+  const c32* ap = (second ? P.A1 : P.A0) + (long)b * P.sA + (long)row * P.lda + 4 * g;
+  const c32* xp[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int v = v0 + 16 * j + r16 < P.nvec ? v0 + 16 * j + r16 : P.nvec - 1;
+    xp[j] = (second ? P.X1 : P.X0) + (long)b * P.sx + (long)v * P.ldx + 4 * g;
+  }
+  f4 rr[NT], ii[NT], ri[NT], ir[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) rr[j] = ii[j] = ri[j] = ir[j] = f4{0, 0, 0, 0};
+  auto chunk = [&](const f4 (&a)[2], const f4 (&x)[NT][2]) {
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+      const float ar = a[st >> 1][2 * (st & 1)], ai = a[st >> 1][2 * (st & 1) + 1];
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        const float xr = x[j][st >> 1][2 * (st & 1)], xi = x[j][st >> 1][2 * (st & 1) + 1];
+        rr[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, xr, rr[j], 0, 0, 0);
+        ii[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai, xi, ii[j], 0, 0, 0);
+        ri[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, xi, ri[j], 0, 0, 0);
+        ir[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai, xr, ir[j], 0, 0, 0);
+      }
+    }
+  };
+  const int nfull = P.K / 16;
+#pragma unroll 2
+  for (int c = wave; c < nfull; c += KS) {
+    f4 a[2], x[NT][2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      a[q] = *reinterpret_cast<const f4u*>(ap + 16 * c + 2 * q);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) x[j][q] = *reinterpret_cast<const f4u*>(xp[j] + 16 * c + 2 * q);
+    }
+    chunk(a, x);
+  }
+  if (16 * nfull < P.K && nfull % KS == wave) {  // the last, partial chunk: zeros past K
+    f4 a[2], x[NT][2];
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+      const bool in = 16 * nfull + 4 * g + st < P.K;
+      const c32 av = in ? ap[16 * nfull + st] : mk<float>(0, 0);
+      a[st >> 1][2 * (st & 1)] = av.x;
+      a[st >> 1][2 * (st & 1) + 1] = av.y;
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        const c32 xv = in ? xp[j][16 * nfull + st] : mk<float>(0, 0);
+        x[j][st >> 1][2 * (st & 1)] = xv.x;
+        x[j][st >> 1][2 * (st & 1) + 1] = xv.y;
+      }
+    }
+    chunk(a, x);
+  }
+  // register q of lane l holds row 4 (l / 16) + q, vector l % 16
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      red[wave][16 * j + r16][2 * (4 * g + q)] = rr[j][q] - ii[j][q];
+      red[wave][16 * j + r16][2 * (4 * g + q) + 1] = ri[j][q] + ir[j][q];
+    }
+  __syncthreads();
+  for (int o = threadIdx.x; o < 256 * NT; o += 64 * KS) {
+    const int i = m0 + (o & 15), v = v0 + (o >> 4);
+    if (i >= M || v >= P.nvec) continue;
+    c32 s = mk<float>(red[0][o >> 4][2 * (o & 15)], red[0][o >> 4][2 * (o & 15) + 1]);
+#pragma unroll
+    for (int w = 1; w < KS; ++w) s = s + mk<float>(red[w][o >> 4][2 * (o & 15)], red[w][o >> 4][2 * (o & 15) + 1]);
+    const long at = i + (second ? P.M0 : 0);
+    c32 y = P.alpha * s;
+    if (P.Z && (P.beta.x != 0.f || P.beta.y != 0.f)) y = y + P.beta * P.Z[(long)b * P.sz + (long)v * P.ldz + at];
+    P.Y[(long)b * P.sy + (long)v * P.ldy + at] = y;
+  }
+}
+
+// Two of the 16-wide vector groups share A's loads from 17 vectors on; more
+// wavefronts split K where four a workgroup would leave the device half empty
+// (limits of 512 and 2048 workgroups, or 64 and 256 for K: within 1 %).
+static void cskinny(hipStream_t s, SkinnyP P, int nprob) {
+  P.t0 = ceil_div(P.M0, 16);
+  P.tiles = P.t0 + ceil_div(P.M1, 16);
+  const int nt = P.nvec > 16 ? 2 : 1;
+  const long wgs = (long)P.tiles * nprob;
+  LSH_REQUIRE(wgs <= 2147483647L && ceil_div(P.nvec, 16 * nt) <= 65535, -6, "cskinny: too many rows or vectors");
+  const dim3 grid((unsigned)wgs, (unsigned)ceil_div(P.nvec, 16 * nt));
+  const bool deep = wgs * grid.y < 1024 && P.K > 128;
+  if (nt == 1) {
+    if (deep) hipLaunchKernelGGL((k_cskinny<1, 16>), grid, dim3(1024), 0, s, P);
+    else hipLaunchKernelGGL((k_cskinny<1, 4>), grid, dim3(256), 0, s, P);
+  } else {
+    if (deep) hipLaunchKernelGGL((k_cskinny<2, 8>), grid, dim3(512), 0, s, P);
+    else hipLaunchKernelGGL((k_cskinny<2, 4>), grid, dim3(256), 0, s, P);
+  }
+  LSH_LAUNCH_CHECK();
+}
+constexpr int kSkinnyMin = 3;  // vectors (one or two: the row-streaming kernels, which leave no lane idle)
+
 // ---------------------------------------------------------------- GEMV
 // One wavefront per row, lanes stride the row (coalesced); x_b staged in LDS.
 
@@ -971,13 +1109,26 @@ void cgemv(hipStream_t s, int M, int N, cplx<R> alpha,
                (double)sizeof(cplx<R>) * ((double)nmat * M * N + (double)batch * (N + (z ? 2.0 : 1.0) * M)));
   const int am = amod > 0 ? amod : 1;
   if (batch > am && batch % am == 0 && batch / am <= 64) {
-    // several vectors per matrix: groups of four read each matrix once
     const int nvec = batch / am;
-    for (int v0 = 0; v0 < nvec; v0 += 4) {
-      const int nv = nvec - v0 < 4 ? nvec - v0 : 4;
+    if constexpr (sizeof(R) == 4)
+      if (nvec >= kSkinnyMin) {
+        SkinnyP P;
+        P.M0 = M; P.M1 = 0; P.K = N; P.nvec = nvec;
+        P.alpha = alpha; P.beta = beta;
+        P.A0 = P.A1 = A; P.lda = lda; P.sA = sA;
+        P.X0 = P.X1 = x; P.sx = sx; P.ldx = am * sx;
+        P.Z = z; P.sz = sz; P.ldz = am * sz;
+        P.Y = y; P.sy = sy; P.ldy = am * sy;
+        cskinny(s, P, am);
+        return;
+      }
+    // several vectors per matrix: groups of four (FP32: the two that the tiles above leave) read each matrix once
+    constexpr int G = sizeof(R) == 4 ? kSkinnyMin - 1 : 4;
+    for (int v0 = 0; v0 < nvec; v0 += G) {
+      const int nv = nvec - v0 < G ? nvec - v0 : G;
       const long o = (long)v0 * am;
       const cplx<R>* zv = z ? z + o * sz : nullptr;
-      cgemv_dispatch<R, 4>(s, M, N, alpha, A, lda, sA, am, nv, x + o * sx, sx, beta, zv, sz, y + o * sy, sy,
+      cgemv_dispatch<R, G>(s, M, N, alpha, A, lda, sA, am, nv, x + o * sx, sx, beta, zv, sz, y + o * sy, sy,
                            (long)am * M);
       LSH_LAUNCH_CHECK();
     }
@@ -1113,6 +1264,18 @@ void cmgemv2(hipStream_t s, int Rr, int R1, long xoff2, int C, cplx<R> alpha, co
   ProfScope ps(sizeof(R) == 4 ? "cmgemv_f32" : "cmgemv_f64", s,
                (double)sizeof(cplx<R>) * ((double)Rr * C + (double)nvec * ((R1 < Rr ? 2.0 : 1.0) * C +
                                                                           (Z ? 2.0 : 1.0) * Rr)));
+  if constexpr (sizeof(R) == 4)
+    if (nvec >= kSkinnyMin) {
+      SkinnyP P;
+      P.M0 = R1; P.M1 = Rr - R1; P.K = C; P.nvec = nvec;
+      P.alpha = alpha; P.beta = beta;
+      P.A0 = Mat; P.A1 = Mat2; P.lda = ldm; P.sA = 0;
+      P.X0 = X; P.X1 = X + xoff2; P.sx = 0; P.ldx = ldx;
+      P.Z = Z; P.sz = 0; P.ldz = ldz;
+      P.Y = Y; P.sy = 0; P.ldy = ldy;
+      cskinny(s, P, 1);
+      return;
+    }
   constexpr int RR = sizeof(R) == 4 ? 4 : 2;  // (FP64: the accumulators in half the rows)
   // Launches that would give fewer than two workgroups per compute unit take
   // one row per wave instead (each row's sum is the same either way).
@@ -1125,8 +1288,10 @@ void cmgemv2(hipStream_t s, int Rr, int R1, long xoff2, int C, cplx<R> alpha, co
 #define LSH_MG_NV(RRV, WSS)           \
   if (nvs == 1) LSH_MG(RRV, 1, WSS);  \
   else if (nvs == 2) LSH_MG(RRV, 2, WSS); \
-  else if (nvs == 4) LSH_MG(RRV, 4, WSS); \
-  else LSH_MG(RRV, 8, WSS);
+  else if constexpr (sizeof(R) == 8) {    \
+    if (nvs == 4) LSH_MG(RRV, 4, WSS);    \
+    else LSH_MG(RRV, 8, WSS);             \
+  }
   if (C >= 1024) {
     if (thin) { LSH_MG_NV(1, 4) }
     else { LSH_MG_NV(RR, 4) }

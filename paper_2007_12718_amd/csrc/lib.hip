@@ -51,11 +51,12 @@ using namespace lsh;
 // not be too large for one compute unit: to c = 128 the launches saved are
 // worth more even with a few boxes (apply on 64 x 64: 232 us unfused below 128
 // vectors, 141 fused; on 256 x 256: 398 against 371, and 412 with c = 188 and
-// 16 boxes fused as well), to c = 256 from 128 box vectors on (c = 252, 128
-// boxes: 160 us either way; 32 boxes with 8 right-hand sides: 150 against 193;
-// c = 377, 16 boxes with 8: 313 against 232).  lsh_apply_fused_levels sets one
-// threshold on the box vectors instead (0: never; -1: this rule).
-constexpr int kApplyFusedSmall = 128, kApplyFusedMost = 256, kApplyFusedMin = 128;
+// 16 boxes fused as well), to c = 200 from 128 box vectors on (one solve on
+// 1024 x 1024: 13.4 ms, with the limit at 128 13.6 and at 256, which takes in
+// c = 252 with 128 boxes, 13.6; 8 fields on 512 x 512: 11.15, 11.1 and 11.5).
+// lsh_apply_fused_levels sets one threshold on the box vectors instead (0:
+// never; -1: this rule).
+constexpr int kApplyFusedSmall = 128, kApplyFusedMost = 200, kApplyFusedMin = 128;
 static int g_apply_fused_min = -1;
 
 namespace {
