@@ -68,7 +68,7 @@ def parse():
                          "workload family at the same kappa h): 10th-order HBS, FP64, applied once")
     ap.add_argument("--direct-tol", type=float, default=1e-6,
                     help="compression tolerance of the direct-solver mode (below 1e-7 the row IDs use the "
-                         "one-workgroup CPQR, which is slow at large ranks)")
+                         "Householder CPQR, a launch per pivot: slower at large ranks)")
     ap.add_argument("--plan-cache", action="store_true",
                     help="instead of the headline run: the same step for a new b each time with the row IDs "
                          "taken from the plan cache (filled by the warmup), as in an inverse problem")
@@ -606,15 +606,13 @@ def main():
     med = head["median"]
     its = max(med["iterations"], 1)
     ab = apply_bytes(w.n, w.leaf, med["ranks"], med["lowrank_ranks"], 8)
-    Mfft = 1
-    while Mfft < 2 * w.n:
-        Mfft *= 2
+    Mfft = min(r * 2 ** k for r in (1, 3, 5) for k in range(32) if r * 2 ** k >= 2 * w.n)  # the transforms' length
     Hq = Mfft // 2 + 1
     ob = 16.0 * 2 * w.n ** 2 + 8.0 * w.n ** 2 + 16.0 * Hq ** 2   # x, y, b once and the spectrum quarter once
-    # what the five passes move (row transform, transpose, column transform with
-    # the spectrum, transpose, inverse row transform with the epilogue): the
-    # n x M intermediate is written and read four times
-    pb = 16.0 * w.n ** 2 + 16.0 * 8 * w.n * Mfft + 16.0 * Hq ** 2 + 40.0 * w.n ** 2
+    # what the three passes move (rows stored transposed, columns with the spectrum
+    # stored transposed, inverse rows with the epilogue): x, the n x M intermediate
+    # written and read twice, the spectrum quarter, then x, b and y
+    pb = 16.0 * w.n ** 2 + 64.0 * w.n * Mfft + 16.0 * Hq ** 2 + 40.0 * w.n ** 2
     t_ap, t_op = med["solve_ms_precond"] / its, med["solve_ms_operator"] / its
     out["solve_streams"] = {
         "apply_ms": t_ap, "apply_algorithmic_GB": ab / 1e9, "apply_GBs": ab / (t_ap * 1e-3) / 1e9,
