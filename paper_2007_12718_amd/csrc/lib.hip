@@ -2157,9 +2157,9 @@ constexpr int EV_NT = 256, EV_MAXRHS = 8;
 // Sums over one part of the grid for PT points (blockIdx.x) and NR fields:
 // a workgroup takes the nodes [blockIdx.y * chunk, ...), so that a few
 // receivers still fill the chip; PT points share each node's fields.  The
-// sums go to part[part][pt][r], or to out where one part is the whole grid.  One workgroup per receiver over the whole
-// grid with the library's j0 and y0 took 1.74 ms for 64 receivers and 8
-// fields on 512 x 512; this takes 0.165 ms.
+// sums go to part[part][pt][r], or to out where one part is the whole grid.
+// One workgroup per receiver over the whole grid with the library's j0 and y0
+// took 1.74 ms for 64 receivers and 8 fields on 512 x 512; this takes 0.165 ms.
 template <int NR, int PT>
 __global__ __launch_bounds__(EV_NT) void k_eval_points(const z64* __restrict__ sig, int n, double h, double gx0,
                                                        double gy0, double kappa, const double* __restrict__ xy,
