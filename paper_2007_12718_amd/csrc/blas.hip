@@ -485,8 +485,8 @@ static void launch_gemm(hipStream_t s, const GemmP<R>& P, const cplx<R>* A, cons
                         cplx<R>* C, long sA, long sB, long sD, long sC, int batch) {
   constexpr int BM = 32 * WM, BN = 32 * WN;
   const char* name = sizeof(R) == 4 ? (BM == 128 ? "cgemm_f32_128x128" : "cgemm_f32_64x64")
-                                    : (BM == 128 ? "cgemm_f64_128x64" : BK == 32 ? "cgemm_f64_64x64k32"
-                                                                                 : "cgemm_f64_64x64");
+                                    : (BM == 128 ? "cgemm_f64_128x64" : BM == 32 ? "cgemm_f64_32x32k32"
+                                       : BK == 32 ? "cgemm_f64_64x64k32" : "cgemm_f64_64x64");
   for (int b0 = 0; b0 < batch; b0 += 65535) {
     int nb = batch - b0 < 65535 ? batch - b0 : 65535;
     // algorithmic bytes: each distinct operand once, the result (and D) once per problem
@@ -505,7 +505,7 @@ static void launch_gemm(hipStream_t s, const GemmP<R>& P, const cplx<R>* A, cons
 
 // ---- GEMM variants and their choice
 //
-// FP32: tile (64 WM) x (64 WN) with K depth BK.  FP64: 64 x 64 (16 or 32 deep) or 128 x 64.
+// FP32: tile (64 WM) x (64 WN) with K depth BK.  FP64: 64 x 64 (16 or 32 deep), 128 x 64 or 32 x 32.
 // All variants of one precision add the same products in the same order, so
 // the choice changes the time, never the bits.
 struct GemmVariant { int wm, wn, bk; const char* name; };
@@ -513,7 +513,8 @@ static const GemmVariant kF32Variants[] = {
     {1, 1, 32, "cgemm_f32_64x64"},   {2, 1, 32, "cgemm_f32_128x64"},    {2, 2, 32, "cgemm_f32_128x128"},
     {1, 1, 64, "cgemm_f32_64x64k64"}, {2, 1, 64, "cgemm_f32_128x64k64"}, {1, 2, 32, "cgemm_f32_64x128"}};
 static const GemmVariant kF64Variants[] = {
-    {2, 2, 16, "cgemm_f64_64x64"}, {4, 2, 16, "cgemm_f64_128x64"}, {2, 2, 32, "cgemm_f64_64x64k32"}};
+    {2, 2, 16, "cgemm_f64_64x64"}, {4, 2, 16, "cgemm_f64_128x64"}, {2, 2, 32, "cgemm_f64_64x64k32"},
+    {1, 1, 32, "cgemm_f64_32x32k32"}};
 constexpr int kNumF32Variants = sizeof(kF32Variants) / sizeof(kF32Variants[0]);
 constexpr int kNumF64Variants = sizeof(kF64Variants) / sizeof(kF64Variants[0]);
 
@@ -527,14 +528,25 @@ const char* gemm_variant_name(int prec, int v) {
 // round costs (resident workgroups x tile area) / (per-CU efficiency of that
 // tile)), from rates of 168 TF/s for the 128 x 64 tile and 160 for 64 x 64 at
 // 4096^3, 120 against 97 for 256 products of order 128, 50 against 85 for 1024
-// of order 64.  For FP64 the 32-deep 64 x 64 tile: 68 TF/s at 4096^3 with
-// either depth, 51 against 48 at 1280^3, 44 against 50 for 1024 products of
-// order 64; 61 and 37 with 128 x 64 tiles.
+// of order 64.  For FP64 see f64_variant.
 struct TileModel { int variant, bm, bn, resident; double eff; };
 static const TileModel kF32Model[2] = {{1, 128, 64, 2, 1.00}, {0, 64, 64, 3, 0.95}};
 
+// FP64, by the number of 64 x 64 output tiles t64 and 32 x 32 ones t32: the
+// small tile, four workgroups to a compute unit, where the large one gives
+// fewer than its two to each (a product alone takes 13 us with 64 x 64 tiles and 6 with 32 x 32 at
+// order 64, 80 and 29 at 512, 335 and 312 at 1000 x 1000 x 2000), and past that
+// where its rounds come out shorter (1600^3, 625 tiles: 636 and 530 us; 2000 x
+// 1000 x 1000, 512 tiles: 288 and 290).  The 32-deep stages: 68 TF/s at 4096^3
+// with either depth, 51 against 48 at 1280^3; 61 and 37 with 128 x 64 tiles.
+static int f64_variant(long t64, long t32) {
+  const long r64 = (t64 + 511) / 512, r32 = (t32 + 1023) / 1024;
+  return t64 < 512 || r32 < 2 * r64 ? 3 : 2;
+}
+
 static int model_variant(int prec, int M, int N, int batch) {
-  if (prec != 1) return 2;
+  if (prec != 1)
+    return f64_variant((long)ceil_div(M, 64) * ceil_div(N, 64) * batch, (long)ceil_div(M, 32) * ceil_div(N, 32) * batch);
   int best = 0;
   double bt = 1e300;
   for (const TileModel& tm : kF32Model) {
@@ -669,10 +681,13 @@ void cgemm(hipStream_t s, int M, int N, int K, cplx<R> alpha,
       default: launch_gemm_x32<1, 1, 32>(s, P, A, B, D, C, sA, sB, sD, sC, batch, nm); break;
     }
   } else {
-    // (Hermitian Grams in lower mode: the 32-deep 64 x 64 tile, fastest on every measured shape)
-    const int v = lower ? 2 : choose_variant(0, M, N, K, batch);
+    // (Hermitian Grams in lower mode: the same rule on the tiles that reach the diagonal or below it)
+    const long n64 = ceil_div(M, 64), n32 = ceil_div(M, 32);
+    const int v = lower ? f64_variant(n64 * (n64 + 1) / 2 * batch, n32 * (n32 + 1) / 2 * batch)
+                        : choose_variant(0, M, N, K, batch);
     if (v == 1) launch_gemm<R, 4, 2>(s, P, A, B, D, C, sA, sB, sD, sC, batch);
     else if (v == 2) launch_gemm<R, 2, 2, 32>(s, P, A, B, D, C, sA, sB, sD, sC, batch);
+    else if (v == 3) launch_gemm<R, 1, 1, 32>(s, P, A, B, D, C, sA, sB, sD, sC, batch);
     else launch_gemm<R, 2, 2>(s, P, A, B, D, C, sA, sB, sD, sC, batch);
   }
 }
