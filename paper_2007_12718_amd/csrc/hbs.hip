@@ -8,6 +8,7 @@
 #include <functional>
 #include <vector>
 
+#include "cpqr.hpp"
 #include "hbs.hpp"
 #include "wave.hpp"
 #include "ops.hpp"
@@ -123,11 +124,6 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
 // that of 32 x 32 (order 4) from 17.4 to 6.0 ms.
 constexpr int QR_NT = 1024, QR_NW = QR_NT / 64;
 constexpr int QS_NT = 256, QS_NW = QS_NT / 64;
-// device state of one CPQR: rank, done flag, squared stopping threshold
-struct CpqrState {
-  int k, done;
-  double thr2;
-};
 
 __device__ __forceinline__ double cpqr_block_sum(double v, double* sb, int lane, int wave) {
   v = group_sum<64>(v);
@@ -171,7 +167,7 @@ __global__ __launch_bounds__(QS_NT) void k_cpqr_step(z64* W, int m, int np, int 
                                                       double* nout, int* J, z64* Rd, CpqrState* st) {
   __shared__ double sb[QS_NW], sx[QS_NW], sy[QS_NW];
   __shared__ int si[QS_NW];
-  if (st->done) return;
+  if (st->over(j)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = blockIdx.x;
   z64* w = W + (long)i * np;
   z64 e[NE > 0 ? NE : 1];
@@ -196,10 +192,7 @@ __global__ __launch_bounds__(QS_NT) void k_cpqr_step(z64* W, int m, int np, int 
   for (int v = 1; v < QS_NW; ++v)
     if (sb[v] > best || (sb[v] == best && si[v] < p)) { best = sb[v]; p = si[v]; }
   if (!(best > st->thr2)) {  // (the same in every workgroup)
-    if (i == 0 && tid == 0) {
-      st->k = j;
-      st->done = 1;
-    }
+    if (i == 0 && tid == 0) st->stop(j);
     return;
   }
   const z64* v = W + (long)p * np;

@@ -48,3 +48,21 @@ def test_every_level_is_a_valid_id(n, leaf, order, tol, width, kh):
         d = np.abs(np.diag(R[:, J]))
         assert np.all(d >= tail.max(axis=1) - 1e-13 * fro), (l, m, k)
         assert d.min() > tol * fro - 1e-13 * fro and np.sqrt(left.max()) <= tol * fro + 1e-13 * fro, (l, m, k)
+
+
+def test_plans_repeat_bit_for_bit():
+    """More rows (1396) than workgroups fit the device at once, so that the launch in which the pivoting stops still
+    starts workgroups after the stop is stored: the same pivots and interpolation every time."""
+    import torch
+    from paper_2007_12718_amd import lsh
+    o = dict(op_order=10, leaf=8, tol=1e-10, proxy_width=3, prec="fp64", hbs_order=10, merge="schur")
+    ref = None
+    for _ in range(3):
+        P = lsh.Plan(128, 0.5 * 128, **o)
+        L = P.ranks()[0]
+        got = [P.level(l) for l in range(1, L + 1)]
+        if ref is None:
+            ref = got
+        for (J, _, U), (Jr, _, Ur) in zip(got, ref):
+            assert np.array_equal(J, Jr) and torch.equal(U, Ur)
+        P.close()
