@@ -1241,14 +1241,17 @@ __global__ __launch_bounds__(1024) void k_bp_newcols(z64* Lt, const z64* M, int 
 // units idle (at depth 700 of 750 candidates: 22 us a step with 128, 14 with
 // 64), 128 beyond, where the partial sums' bytes count (n = 1024: 98.5 ms a setup
 // with this line at 1536, 99.8 with 128 everywhere, 100 with 64 everywhere)
-static int bp_kc(int m) { return m <= 1536 ? 64 : 128; }
+constexpr int BP_SHALLOW = 1536;
+static int bp_kc(int m) { return m <= BP_SHALLOW ? 64 : 128; }
 
+// Enough for every row ID of at most m rows: a plan's memory is sized from
+// bounds on m, and BP_SHALLOW rows have more partial sums than a few more.
 size_t rowid_bp_ws(int m) {
   const size_t mm = (size_t)m * m, mp = (size_t)m + BP_KCMAX;
-  const size_t nch = mp / bp_kc(m) + 1;
+  auto wt = [](int r) { return ((size_t)(r + BP_KCMAX) / bp_kc(r) + 1) * BP_NP * r; };
+  const size_t partw = m > BP_SHALLOW ? std::max(wt(m), wt(BP_SHALLOW)) : wt(m);
   return sizeof(z64) * (mm + mp * m + 2 * mm) + sizeof(double) * m + sizeof(int) * (3 * m + BPS_WORDS) +
-         sizeof(z64) * (BP_B * BP_B + 2 * BP_NP * BP_NP + (mp / BP_KCS + 1) * BP_B * BP_B +
-                        nch * (size_t)BP_NP * m) +
+         sizeof(z64) * (BP_B * BP_B + 2 * BP_NP * BP_NP + (mp / BP_KCS + 1) * BP_B * BP_B + partw) +
          inverse_ws_bytes<double>(64, m / 64 + 1) + sizeof(z64) * (size_t)(m / 64 + 1) * 64 * 64 + 32 * 256;
 }
 

@@ -129,6 +129,7 @@ struct lsh_plan_s {
   // overlap it from the other end, is free
   void place_level(int l, size_t need) {
     const int e = (l - d.full_levels) & 1;
+    if (need > sid.cap()) throw Error(LSH_ERR_WORKSPACE_TOO_SMALL, "plan row-ID temporaries exceed their bound");
     bool ok = l + 2 > L || interp_wait(l + 2);
     if (ok && l < L && need + id_need[1 - e] > sid.cap()) ok = interp_wait(l + 1), id_need[1 - e] = 0;
     if (!ok) throw Error(LSH_ERR_HIP, "internal: the build has failed elsewhere");

@@ -75,3 +75,20 @@ def test_builds_on_two_threads():
     assert not err, err
     for i, v in out.items():
         assert all(torch.equal(y, ref[i]) for y in v)
+
+
+def test_a_level_just_below_its_bound():
+    """1510 to 1536 candidates under a bound of 1544: their row ID takes more partial sums than one of 1544 rows."""
+    import torch
+    from paper_2007_12718_amd import lsh
+    n = 384
+    rng = np.random.default_rng(n)
+    b = cuda(synth.bumps(n, rng))
+    x = cuda(rng.standard_normal((1, n, n)) + 1j * rng.standard_normal((1, n, n)))
+    o = dict(op_order=4, leaf=6, tol=1e-4, proxy_width=1, prec="fp32")
+    P = lsh.Plan(n, 0.6 * n, **o)
+    assert 1510 <= 2 * P.ranks()[1][2] <= 1536
+    y = lsh.Factor(P, b).apply_precond(x)
+    P2, F2 = lsh.build(n, 0.6 * n, b, **o)
+    assert P2.ranks() == P.ranks()
+    assert torch.equal(F2.apply_precond(x), y)
