@@ -2160,12 +2160,13 @@ constexpr int EV_NT = 256, EV_MAXRHS = 8;
 // receivers still fill the chip; PT points share each node's fields.  The
 // sums go to part[part][pt][r], or to out where one part is the whole grid.
 // One workgroup per receiver over the whole grid with the library's j0 and y0
-// took 1.74 ms for 64 receivers and 8 fields on 512 x 512; this takes 0.165 ms.
+// took 1.74 ms for 64 receivers and 8 fields on 512 x 512; this takes 0.15 ms.
+// (Wavefronts per SIMD are asked for: left to itself the compiler takes 191
+// registers for the loads of green_h0's table, which is two; 0.163 ms.)
 template <int NR, int PT>
-__global__ __launch_bounds__(EV_NT) void k_eval_points(const z64* __restrict__ sig, int n, double h, double gx0,
-                                                       double gy0, double kappa, const double* __restrict__ xy,
-                                                       z64* __restrict__ part, z64* __restrict__ out, int npts,
-                                                       int nrhs, int chunk) {
+__global__ __launch_bounds__(EV_NT, NR == 8 ? 3 : 4) void k_eval_points(
+    const z64* __restrict__ sig, int n, double h, double gx0, double gy0, double kappa, const double* __restrict__ xy,
+    z64* __restrict__ part, z64* __restrict__ out, int npts, int nrhs, int chunk) {
   __shared__ z64 red[EV_NT / 64][PT * NR];
   const int N = n * n, p0 = blockIdx.x * PT, tid = threadIdx.x;
   double px[PT], py[PT];
@@ -2225,11 +2226,12 @@ __global__ __launch_bounds__(256) void k_points_reduce(const z64* __restrict__ p
 // out[m][j] = h^2 sum_r conj(G(|x_r - x_j|)) g[m][r]  (adjoint of the receiver
 // map): a node per thread, the receivers over PG groups of threads (PG > 1
 // where the nodes alone would leave units idle), each group's sums joined in
-// LDS.  64 receivers, 8 fields, 512 x 512: 1.74 -> 0.154 ms.
+// LDS.  64 receivers, 8 fields, 512 x 512: 1.74 -> 0.13 ms (0.15 with g's
+// values loaded after the kernel value).
 template <int NR, int PG>
-__global__ __launch_bounds__(EV_NT) void k_eval_points_adj(const z64* __restrict__ g, int npts, int nrhs, int n,
-                                                           double h, double gx0, double gy0, double kappa,
-                                                           const double* __restrict__ xy, z64* out) {
+__global__ __launch_bounds__(EV_NT, NR == 8 && PG > 1 ? 3 : 4) void k_eval_points_adj(
+    const z64* __restrict__ g, int npts, int nrhs, int n, double h, double gx0, double gy0, double kappa,
+    const double* __restrict__ xy, z64* out) {
   constexpr int JB = EV_NT / PG;
   __shared__ z64 red[PG > 1 ? PG - 1 : 1][PG > 1 ? NR : 1][PG > 1 ? JB : 1];
   const int N = n * n, jb = threadIdx.x % JB, pg = threadIdx.x / JB;
@@ -2240,10 +2242,13 @@ __global__ __launch_bounds__(EV_NT) void k_eval_points_adj(const z64* __restrict
 #pragma unroll
   for (int m = 0; m < NR; ++m) acc[m] = mk(0.0, 0.0);
   for (int r = pg; r < npts; r += PG) {
+    z64 gv[NR];
+#pragma unroll
+    for (int m = 0; m < NR; ++m) gv[m] = g[(long)(m < nrhs ? m : 0) * npts + r];  // (as above)
     const double dx = xy[2 * r] - px, dy = xy[2 * r + 1] - py;
     const z64 gc = conjg(green_h0(kappa * sqrt(dx * dx + dy * dy)));
 #pragma unroll
-    for (int m = 0; m < NR; ++m) fma_acc(acc[m], gc, g[(long)(m < nrhs ? m : 0) * npts + r]);  // (as above)
+    for (int m = 0; m < NR; ++m) fma_acc(acc[m], gc, gv[m]);
   }
   if (PG > 1) {
     if (pg > 0)

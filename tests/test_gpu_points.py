@@ -96,3 +96,25 @@ def test_calls_on_two_streams_take_turns():
             outs.append(P.eval_points(sig[k % 2], xy))
     torch.cuda.synchronize()
     assert all(torch.equal(o, ref[k % 2]) for k, o in enumerate(outs))
+
+
+@pytest.mark.parametrize("lo,hi,tol", [(1e-8, 0.5, 3.5e-16), (0.5, 14.0, 1.7e-16), (14.0, 1e4, 5e-16)])
+def test_kernel_values_to_the_last_bits(lo, hi, tol):
+    """Arguments that reach the kernel exactly (kappa = 1, receivers on the axis through a node at 0).  Below 1/2 the
+    logarithm may be off by one unit in the last place and the sum is rounded; up to 14 both parts are rounded once and
+    the terms behind the first, at most an eighth of |H1|, three times; beyond, the stated bound."""
+    mpmath = pytest.importorskip("mpmath")
+    from paper_2007_12718_amd import lsh
+    plan = lsh.Plan(4, 1.0, op_order=4, leaf=2, tol=0.0, proxy_width=1, prec="fp64", h=0.25, x0=-0.125, y0=-0.125)
+    rng = np.random.default_rng(7)
+    r = np.concatenate([lo * (hi / lo) ** rng.random(600), rng.uniform(lo, hi, 600)])
+    edges = np.concatenate([np.arange(8, 16) / 16, np.arange(8, 16) / 8, np.arange(8, 57) / 4])
+    r = np.concatenate([r, np.nextafter(edges, 0), np.nextafter(edges, 99)])
+    r = r[(r >= lo) & (r < hi)]
+    sig = np.zeros((1, 4, 4), complex)
+    sig[0, 0, 0] = 16.0
+    out = plan.eval_points(cuda(sig), cuda(np.stack([r, 0 * r], axis=1))).cpu().numpy()[0]
+    with mpmath.workdps(30):
+        for x, v in zip(r.tolist(), out.tolist()):
+            ref = (1j * mpmath.besselj(0, x) - mpmath.bessely(0, x)) / 4
+            assert abs(mpmath.mpc(v) - ref) <= tol * abs(ref), (x, v)
