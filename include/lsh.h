@@ -38,7 +38,8 @@
  *    are found while the plan is built; lsh_plan_workspace_used reports what
  *    was used); factor and solve sizes are exact for the given plan.
  *  - Handles are small host objects; destroy them with the matching
- *    *_destroy call (host only; the workspace stays the caller's).  A
+ *    *_destroy call (host only, but lsh_plan_destroy waits for the work of
+ *    the plan's lsh_eval_points calls; the workspace stays the caller's).  A
  *    factor refers to its plan: destroy the factor first.
  *  - The stream is a hipStream_t passed as void* (NULL = the null stream).
  *    Calls that must read back small device values synchronise the stream
@@ -295,7 +296,9 @@ int lsh_solve_adjoint(lsh_factor_t factor, const void* g, int nrhs, void* lambda
 
 /* u(x_r) = h^2 sum_j (i/4) H0(kappa |x_r - x_j|) sigma_j at off-grid points
  * (eq. (ansatz), trapezoidal sum).  xy: device double[2*npts];
- * u_pts: device double2[nrhs*npts]. */
+ * u_pts: device double2[nrhs*npts].  Partial sums lie in the plan's workspace,
+ * where the calls of one plan take turns on the device, also from several
+ * streams or host threads; a call on a stream under capture uses none. */
 int lsh_eval_points(lsh_plan_t plan, const void* sigma, const double* xy, int npts, void* u_pts, int nrhs,
                     void* stream);
 

@@ -152,9 +152,11 @@ struct lsh_plan_s {
   std::vector<I2> ng_prox;  // (host source of its proxy upload)
   ConvOperator op;
   // The row-ID temporaries (sid) are free once the plan is built; the receiver
-  // sums use them for partial results.  A call waits on the stream for the
-  // previous call's event, so calls on different streams take turns there;
-  // the plan's end waits for the last one.
+  // sums use them for partial results.  A call waits on its stream for the
+  // previous call's event and records its own, holding pts_mu from the one to
+  // the other, so that calls on different streams and from different threads
+  // take turns there; the plan's end waits for the last one.
+  std::mutex pts_mu;
   hipEvent_t pts_ev = nullptr;
   ~lsh_plan_s() {
     if (pts_ev) {
@@ -2212,6 +2214,33 @@ __global__ __launch_bounds__(EV_NT, NR == 8 ? 3 : 4) void k_eval_points(
   }
 }
 
+// A receiver call's turn at the plan's idle memory, from take() to the end of
+// the call (also where it ends by an exception, with launches queued).
+struct PointsTurn {
+  lsh_plan_s* P;
+  hipStream_t s;
+  std::unique_lock<std::mutex> held{};
+  // the memory, ordered on s behind the last turn; null while s is captured
+  z64* take() {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    std::unique_lock<std::mutex> g(P->pts_mu);
+    if (!P->pts_ev) LSH_HIP(hipEventCreateWithFlags(&P->pts_ev, hipEventDisableTiming));
+    LSH_HIP(hipStreamWaitEvent(s, P->pts_ev, 0));  // (nothing before its first record)
+    held = std::move(g);
+    return reinterpret_cast<z64*>(P->sid.base());
+  }
+  ~PointsTurn() {
+    if (held && hipEventRecord(P->pts_ev, s) != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipStreamSynchronize(s);
+    }
+  }
+};
+
 // out[r][pt] = h^2 sum over the parts, one wave per value, in a fixed order
 __global__ __launch_bounds__(256) void k_points_reduce(const z64* __restrict__ part, int parts, int npts, int nrhs,
                                                        double h2, z64* out) {
@@ -3767,18 +3796,8 @@ int lsh_eval_points(lsh_plan_t P, const void* sigma, const double* xy, int npts,
   const long N = (long)P->n * P->n;
   // partial sums in the plan's idle row-ID memory (not under capture, where
   // the turns between calls could not be ordered)
+  PointsTurn turn{P, s};
   z64* scratch = nullptr;
-  auto turn = [&] {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-      (void)hipGetLastError();
-      return false;
-    }
-    if (!P->pts_ev) LSH_HIP(hipEventCreateWithFlags(&P->pts_ev, hipEventDisableTiming));
-    else LSH_HIP(hipStreamWaitEvent(s, P->pts_ev, 0));
-    scratch = reinterpret_cast<z64*>(P->sid.base());
-    return true;
-  };
   for (int r0 = 0; r0 < nrhs; r0 += EV_MAXRHS) {
     const int nr = nrhs - r0 < EV_MAXRHS ? nrhs - r0 : EV_MAXRHS;
     const z64* sg = static_cast<const z64*>(sigma) + r0 * N;
@@ -3788,7 +3807,7 @@ int lsh_eval_points(lsh_plan_t P, const void* sigma, const double* xy, int npts,
       const int groups = ceil_div(npts, pt);
       const size_t each = sizeof(z64) * (size_t)npts * nr;
       long parts = std::min<long>({2048 / groups, N / (4 * EV_NT), (long)(P->sid.cap() / each)});
-      if (parts > 1 && !scratch && !turn()) parts = 1;
+      if (parts > 1 && !scratch && !(scratch = turn.take())) parts = 1;
       const int chunk = ceil_div(ceil_div(N, std::max(1L, parts)), EV_NT) * EV_NT;
       parts = ceil_div(N, chunk);
       z64* direct = parts > 1 ? nullptr : o;
@@ -3805,7 +3824,6 @@ int lsh_eval_points(lsh_plan_t P, const void* sigma, const double* xy, int npts,
     else if (nr <= 4) go(k_eval_points<4, 2>, 2);
     else go(k_eval_points<8, 2>, 2);
   }
-  if (scratch) LSH_HIP(hipEventRecord(P->pts_ev, s));
   return LSH_OK;
   API_END
 }

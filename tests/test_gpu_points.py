@@ -118,3 +118,37 @@ def test_kernel_values_to_the_last_bits(lo, hi, tol):
         for x, v in zip(r.tolist(), out.tolist()):
             ref = (1j * mpmath.besselj(0, x) - mpmath.bessely(0, x)) / 4
             assert abs(mpmath.mpc(v) - ref) <= tol * abs(ref), (x, v)
+
+
+def test_calls_from_two_threads_take_turns():
+    """The same from two host threads, each on its own stream."""
+    import threading
+
+    import torch
+    from paper_2007_12718_amd import lsh
+    n, nrhs = 256, 8
+    P = lsh.Plan(n, 100.0, op_order=4, leaf=8, tol=1e-2, proxy_width=1, prec="fp64")
+    rng = np.random.default_rng(5)
+    t = rng.uniform(0, 2 * np.pi, 33)
+    xy = cuda(np.stack([0.8 * np.cos(t), 0.8 * np.sin(t)], axis=1))
+    sig = [cuda(rng.standard_normal((nrhs, n, n)) + 1j * rng.standard_normal((nrhs, n, n))) for _ in range(2)]
+    ref = [P.eval_points(s, xy) for s in sig]
+    torch.cuda.synchronize()
+    outs, err = [[], []], []
+
+    def calls(i):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                outs[i] = [P.eval_points(sig[i], xy) for _ in range(50)]
+                torch.cuda.current_stream().synchronize()
+        except Exception as e:  # (reported by the main thread)
+            err.append(e)
+
+    ths = [threading.Thread(target=calls, args=(i,)) for i in range(2)]
+    for th in ths:
+        th.start()
+    for th in ths:
+        th.join()
+    assert not err, err
+    for i in range(2):
+        assert len(outs[i]) == 50 and all(torch.equal(o, ref[i]) for o in outs[i])
