@@ -2157,8 +2157,19 @@ void fgmres_multi(lsh_factor_s& F, SolveWs& W, const z64* f, z64* x, int nr, con
 // NR right-hand sides.
 constexpr int EV_NT = 256, EV_MAXRHS = 8;
 
-// Sums over one part of the grid for PT points (blockIdx.x) and NR fields:
-// a workgroup takes the nodes [blockIdx.y * chunk, ...), so that a few
+// Fields of one launch from the `left` that are left: whole groups of
+// EV_MAXRHS on grid z (one launch for 16 fields: adjoint on 16 x 16 with one
+// receiver 21 us with two, 16 with one), the rest in a launch of the
+// template that fits it, unless the call is so small that the launch costs
+// more than the idle part of a last group (2^20 kernel values take 8 us).
+int points_fields(long left, double pairs) {
+  if (left <= EV_MAXRHS) return (int)left;
+  const long most = 4096L * EV_MAXRHS, n = left < most ? left : most;
+  return (int)(pairs <= (double)(1 << 20) ? n : n / EV_MAXRHS * EV_MAXRHS);
+}
+
+// Sums over one part of the grid for PT points (blockIdx.x) and NR fields
+// (blockIdx.z): a workgroup takes the nodes [blockIdx.y * chunk, ...), so that a few
 // receivers still fill the chip; PT points share each node's fields.  The
 // sums go to part[part][pt][r], or to out where one part is the whole grid.
 // One workgroup per receiver over the whole grid with the library's j0 and y0
@@ -2170,7 +2181,9 @@ __global__ __launch_bounds__(EV_NT, NR == 8 ? 3 : 4) void k_eval_points(
     const z64* __restrict__ sig, int n, double h, double gx0, double gy0, double kappa, const double* __restrict__ xy,
     z64* __restrict__ part, z64* __restrict__ out, int npts, int nrhs, int chunk) {
   __shared__ z64 red[EV_NT / 64][PT * NR];
-  const int N = n * n, p0 = blockIdx.x * PT, tid = threadIdx.x;
+  const int N = n * n, p0 = blockIdx.x * PT, tid = threadIdx.x, f0 = blockIdx.z * NR;
+  const int nf = nrhs - f0 < NR ? nrhs - f0 : NR;
+  sig += (long)f0 * N;
   double px[PT], py[PT];
   z64 acc[PT][NR];
 #pragma unroll
@@ -2186,7 +2199,7 @@ __global__ __launch_bounds__(EV_NT, NR == 8 ? 3 : 4) void k_eval_points(
     const int i2 = j / n, i1 = j - i2 * n;
     z64 sv[NR];
 #pragma unroll
-    for (int r = 0; r < NR; ++r) sv[r] = sig[(long)(r < nrhs ? r : 0) * N + j];  // (past nrhs: not stored)
+    for (int r = 0; r < NR; ++r) sv[r] = sig[(long)(r < nf ? r : 0) * N + j];  // (past nf: not stored)
     const double gx = gx0 + (i1 + 0.5) * h, gy = gy0 + (i2 + 0.5) * h;
 #pragma unroll
     for (int p = 0; p < PT; ++p) {
@@ -2207,9 +2220,9 @@ __global__ __launch_bounds__(EV_NT, NR == 8 ? 3 : 4) void k_eval_points(
   if (tid < PT * NR) {
     const int pt = p0 + tid / NR, r = tid % NR;
     const z64 v = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
-    if (pt < npts && r < nrhs) {
-      if (out) out[(long)r * npts + pt] = (h * h) * v;
-      else part[((long)blockIdx.y * npts + pt) * nrhs + r] = v;
+    if (pt < npts && r < nf) {
+      if (out) out[(long)(f0 + r) * npts + pt] = (h * h) * v;
+      else part[((long)blockIdx.y * npts + pt) * nrhs + f0 + r] = v;
     }
   }
 }
@@ -2264,7 +2277,9 @@ __global__ __launch_bounds__(EV_NT, NR == 8 && PG > 1 ? 3 : 4) void k_eval_point
   constexpr int JB = EV_NT / PG;
   __shared__ z64 red[PG > 1 ? PG - 1 : 1][PG > 1 ? NR : 1][PG > 1 ? JB : 1];
   const int N = n * n, jb = threadIdx.x % JB, pg = threadIdx.x / JB;
-  const int j = blockIdx.x * JB + jb;
+  const int j = blockIdx.x * JB + jb, f0 = blockIdx.y * NR, nf = nrhs - f0 < NR ? nrhs - f0 : NR;
+  g += (long)f0 * npts;
+  out += (long)f0 * N;
   const int i2 = j / n, i1 = j - i2 * n;
   const double px = gx0 + (i1 + 0.5) * h, py = gy0 + (i2 + 0.5) * h;
   z64 acc[NR];
@@ -2273,7 +2288,7 @@ __global__ __launch_bounds__(EV_NT, NR == 8 && PG > 1 ? 3 : 4) void k_eval_point
   for (int r = pg; r < npts; r += PG) {
     z64 gv[NR];
 #pragma unroll
-    for (int m = 0; m < NR; ++m) gv[m] = g[(long)(m < nrhs ? m : 0) * npts + r];  // (as above)
+    for (int m = 0; m < NR; ++m) gv[m] = g[(long)(m < nf ? m : 0) * npts + r];  // (as above)
     const double dx = xy[2 * r] - px, dy = xy[2 * r + 1] - py;
     const z64 gc = conjg(green_h0(kappa * sqrt(dx * dx + dy * dy)));
 #pragma unroll
@@ -2293,7 +2308,7 @@ __global__ __launch_bounds__(EV_NT, NR == 8 && PG > 1 ? 3 : 4) void k_eval_point
   if (j < N)
 #pragma unroll
     for (int m = 0; m < NR; ++m)
-      if (m < nrhs) out[(long)m * N + j] = (h * h) * acc[m];
+      if (m < nf) out[(long)m * N + j] = (h * h) * acc[m];
 }
 
 // grad[k] = -kappa^2 Re sum_m conj(lambda[m][k]) (u_inc[m][k] + u[m][k])
@@ -2472,18 +2487,19 @@ int lsh_eval_points_adjoint(lsh_plan_t P, const void* g_pts, const double* xy, i
   LSH_REQUIRE(P && g_pts && xy && out && npts >= 1 && nrhs >= 1, LSH_ERR_INVALID_ARG, "bad argument");
   hipStream_t s = (hipStream_t)stream;
   const long N = (long)P->n * P->n;
-  for (int r0 = 0; r0 < nrhs; r0 += EV_MAXRHS) {
-    const int nr = nrhs - r0 < EV_MAXRHS ? nrhs - r0 : EV_MAXRHS;
+  for (int r0 = 0, nr; r0 < nrhs; r0 += nr) {
+    nr = points_fields(nrhs - r0, (double)N * npts);
+    const int fg = ceil_div(nr, EV_MAXRHS);
     const z64* g = static_cast<const z64*>(g_pts) + (long)r0 * npts;
     z64* o = static_cast<z64*>(out) + r0 * N;
     // up to 2^17 nodes (eight waves a compute unit) four groups of threads share the receivers
     const bool split = N <= (1 << 17);
     auto go = [&](auto k1, auto k4) {
       if (split)
-        hipLaunchKernelGGL(k4, dim3(ceil_div(N, EV_NT / 4)), dim3(EV_NT), 0, s, g, npts, nr, P->n, P->h, P->d.x0,
+        hipLaunchKernelGGL(k4, dim3(ceil_div(N, EV_NT / 4), fg), dim3(EV_NT), 0, s, g, npts, nr, P->n, P->h, P->d.x0,
                            P->d.y0, P->kappa, xy, o);
       else
-        hipLaunchKernelGGL(k1, dim3(ceil_div(N, EV_NT)), dim3(EV_NT), 0, s, g, npts, nr, P->n, P->h, P->d.x0,
+        hipLaunchKernelGGL(k1, dim3(ceil_div(N, EV_NT), fg), dim3(EV_NT), 0, s, g, npts, nr, P->n, P->h, P->d.x0,
                            P->d.y0, P->kappa, xy, o);
     };
     if (nr == 1) go(k_eval_points_adj<1, 1>, k_eval_points_adj<1, 4>);
@@ -3798,20 +3814,21 @@ int lsh_eval_points(lsh_plan_t P, const void* sigma, const double* xy, int npts,
   // the turns between calls could not be ordered)
   PointsTurn turn{P, s};
   z64* scratch = nullptr;
-  for (int r0 = 0; r0 < nrhs; r0 += EV_MAXRHS) {
-    const int nr = nrhs - r0 < EV_MAXRHS ? nrhs - r0 : EV_MAXRHS;
+  for (int r0 = 0, nr; r0 < nrhs; r0 += nr) {
+    nr = points_fields(nrhs - r0, (double)N * npts);
+    const int fg = ceil_div(nr, EV_MAXRHS);
     const z64* sg = static_cast<const z64*>(sigma) + r0 * N;
     z64* o = static_cast<z64*>(u_pts) + (long)r0 * npts;
     auto go = [&](auto kern, int pt) {
       // about eight workgroups a compute unit, each thread at least four nodes, within the scratch
       const int groups = ceil_div(npts, pt);
       const size_t each = sizeof(z64) * (size_t)npts * nr;
-      long parts = std::min<long>({2048 / groups, N / (4 * EV_NT), (long)(P->sid.cap() / each)});
+      long parts = std::min<long>({2048L / ((long)groups * fg), N / (4 * EV_NT), (long)(P->sid.cap() / each)});
       if (parts > 1 && !scratch && !(scratch = turn.take())) parts = 1;
       const int chunk = ceil_div(ceil_div(N, std::max(1L, parts)), EV_NT) * EV_NT;
       parts = ceil_div(N, chunk);
       z64* direct = parts > 1 ? nullptr : o;
-      hipLaunchKernelGGL(kern, dim3(groups, parts), dim3(EV_NT), 0, s, sg, P->n, P->h, P->d.x0, P->d.y0, P->kappa,
+      hipLaunchKernelGGL(kern, dim3(groups, parts, fg), dim3(EV_NT), 0, s, sg, P->n, P->h, P->d.x0, P->d.y0, P->kappa,
                          xy, scratch, direct, npts, nr, chunk);
       LSH_LAUNCH_CHECK();
       if (direct) return;

@@ -152,3 +152,23 @@ def test_calls_from_two_threads_take_turns():
     assert not err, err
     for i in range(2):
         assert len(outs[i]) == 50 and all(torch.equal(o, ref[i]) for o in outs[i])
+
+
+@pytest.mark.parametrize("n,leaf,npts,nrhs", [(16, 4, 1, 16), (64, 8, 3, 17), (384, 6, 9, 17), (384, 6, 9, 24)])
+def test_groups_of_fields_on_the_grid(n, leaf, npts, nrhs):
+    """Whole groups of eight in one launch, with a partial last one (small calls) or that one by itself."""
+    from paper_2007_12718_amd import lsh
+    rng = np.random.default_rng(nrhs)
+    t = rng.uniform(0, 2 * np.pi, npts)
+    pts = np.stack([0.8 * np.cos(t), 0.8 * np.sin(t)], axis=1)
+    sig = rng.standard_normal((nrhs, n, n)) + 1j * rng.standard_normal((nrhs, n, n))
+    g = rng.standard_normal((nrhs, npts)) + 1j * rng.standard_normal((nrhs, npts))
+    P = lsh.Plan(n, 0.5 * n, op_order=4, leaf=leaf, tol=1e-2, proxy_width=1, prec="fp64")
+    E = dense.receiver_matrix(n, 0.5 * n, pts)
+    ref, refb = sig.reshape(nrhs, -1) @ E.T, g @ E.conj()
+    out = P.eval_points(cuda(sig), cuda(pts)).cpu().numpy()
+    back = P.eval_points_adjoint(cuda(g), cuda(pts)).cpu().numpy().reshape(nrhs, -1)
+    tol = 1e-13 * max(1.0, np.sqrt(n) / 8)
+    for r in range(nrhs):
+        assert np.abs(out[r] - ref[r]).max() <= tol * np.abs(ref).max(), r
+        assert np.abs(back[r] - refb[r]).max() <= tol * np.abs(refb).max(), r
