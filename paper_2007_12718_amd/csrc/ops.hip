@@ -119,12 +119,14 @@ void multidot(hipStream_t s, const z64* V, long ldv, int nv, const z64* w, long 
 //   3  |w|^2 = sum p2;  w /= |w| (left alone where that is not positive)
 // Every workgroup adds up the partial sums it needs by itself, which costs
 // less than a launch for them, and step 1's second look at its part of V finds
-// it in L2.  About 256 workgroups in all share the group, one per compute
-// unit, so there are few partial sums.  Bound by the three passes over V (8
-// vectors of 512 x 512 against 6 each: 22 + 36 + 22 + 8 us, V from the memory
-// side's cache at up to 10 TB/s) and on small grids by the launches.  With
-// nine launches for each vector by itself this took some 320 us, and the solve
-// of 8 fields on 512 x 512 14.8 ms against 13.9.
+// it in L2.  About 256 workgroups in all share the vectors still running (bits
+// of active), one per compute unit, so there are few partial sums.  Bound by
+// the three passes over V (8 vectors of 512 x 512 against 6 each: 22 + 36 + 22
+// + 8 us, V from the memory side's cache at up to 10 TB/s) and on small grids
+// by the launches.  With nine launches for each vector by itself this took some
+// 320 us, and the solve of 8 fields on 512 x 512 14.8 ms against 13.9.  (The
+// workgroups go to running vectors only: 30 unpreconditioned iterations for
+// one of eight on 1024 x 1024 take 26.4 ms, 46.7 with an eighth for each.)
 constexpr int CGS_NT = 1024, CGS_E = 4, CGS_WG = 256;
 
 template <int STEP>
@@ -133,14 +135,15 @@ __global__ __launch_bounds__(CGS_NT) void k_cgs(const z64* __restrict__ V, long 
                                                 z64* h, int hs) {
   __shared__ z64 red[STEP <= 1 ? MD_MAXV : 1][CGS_NT / 64];
   __shared__ z64 hv[STEP == 0 ? 1 : MD_MAXV];
-  const int r = blockIdx.y, nb = gridDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (!((active >> r) & 1u)) return;
+  const int q = blockIdx.y, nb = gridDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int k = 0; k < q; ++k) active &= active - 1;
+  const int r = __builtin_ctz(active);  // the q-th running vector
   V += r * N;
   w += r * N;
   if (STEP > 0) {
     const int ns = STEP == 3 ? 1 : nv;
     for (int v = wave; v < ns; v += CGS_NT / 64) {
-      const z64* p = pin + ((long)r * ns + v) * nb;
+      const z64* p = pin + ((long)q * ns + v) * nb;
       z64 a = mk(0.0, 0.0);
       for (int k = lane; k < nb; k += 64) a = a + p[k];
       a = mk(group_sum<64>(a.x), group_sum<64>(a.y));
@@ -209,7 +212,7 @@ __global__ __launch_bounds__(CGS_NT) void k_cgs(const z64* __restrict__ V, long 
   for (int v = tid; v < ns; v += CGS_NT) {
     z64 a = red[v][0];
     for (int k = 1; k < CGS_NT / 64; ++k) a = a + red[v][k];
-    pout[((long)r * ns + v) * nb + blockIdx.x] = a;
+    pout[((long)q * ns + v) * nb + blockIdx.x] = a;
   }
 }
 
@@ -217,10 +220,13 @@ void cgs2(hipStream_t s, const z64* V, long ldv, int nv, z64* w, long N, int nr,
           int hs, z64* partial) {
   ProfScope ps("gram_schmidt", s, 16.0 * (double)N * (3 * nv + 7) * __builtin_popcount(active));
   LSH_REQUIRE(nv <= MD_MAXV && nr >= 1 && nr <= 32, -6, "gram-schmidt: too many vectors");
-  // every workgroup has a piece of the vector: none writes an unset partial sum
-  const int nb = (int)std::max(1L, std::min((long)(CGS_WG / nr), (long)ceil_div(N, (long)(CGS_NT * CGS_E))));
-  z64 *p0 = partial, *p1 = p0 + (size_t)nr * nv * nb, *p2 = p1 + (size_t)nr * nv * nb;  // (at most (2 nv + 1) CGS_WG)
-  const dim3 grid(nb, nr);
+  const int na = __builtin_popcount(active);
+  if (na == 0) return;
+  // the running vectors share the workgroups; every workgroup has a piece of
+  // its vector: none writes an unset partial sum
+  const int nb = (int)std::max(1L, std::min((long)(CGS_WG / na), (long)ceil_div(N, (long)(CGS_NT * CGS_E))));
+  z64 *p0 = partial, *p1 = p0 + (size_t)na * nv * nb, *p2 = p1 + (size_t)na * nv * nb;  // (at most (2 nv + 1) CGS_WG)
+  const dim3 grid(nb, na);
   hipLaunchKernelGGL(k_cgs<0>, grid, dim3(CGS_NT), 0, s, V, ldv, nv, w, N, active, p2, p0, h1, hs);
   LSH_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_cgs<1>, grid, dim3(CGS_NT), 0, s, V, ldv, nv, w, N, active, p0, p1, h1, hs);

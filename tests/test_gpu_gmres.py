@@ -65,3 +65,23 @@ def test_a_group_solves_what_single_runs_solve(n, nrhs):
         assert (sig.reshape(nrhs, n, n)[r] - one).norm() <= 2e-11 * 10 * max(one.norm().item(), 1e-300)
     F.close()
     P.close()
+
+
+# some of eight vectors run, in every position of the others' gaps; one piece of a workgroup and several
+@pytest.mark.parametrize("n", [48, 160])
+@pytest.mark.parametrize("running", [(0,), (7,), (3, 7), (1, 2, 6), (0, 2, 4, 5, 7)])
+def test_vectors_left_in_a_group_solve_what_single_runs_solve(n, running):
+    gen = torch.Generator().manual_seed(n + len(running))
+    b = torch.full((n, n), 0.3, dtype=torch.float64).cuda()
+    P, F = lsh.build(n, 12.0, b, op_order=4, leaf=n // 8 if n == 48 else 10, tol=1e-6, prec="fp64")
+    u = torch.randn(8, n, n, dtype=torch.complex128, generator=gen).cuda()
+    for r in range(8):
+        if r not in running:
+            u[r] = 0
+    sig, _, info, rc = F.solve(u, tol=1e-11, maxit=30, want_u=False)
+    assert rc == 0
+    for r in range(8):
+        one = F.solve(u[r:r + 1], tol=1e-11, maxit=30, want_u=False)[0].reshape(n, n)
+        assert (sig.reshape(8, n, n)[r] - one).norm() <= 2e-11 * 10 * max(one.norm().item(), 1e-300)
+    F.close()
+    P.close()
