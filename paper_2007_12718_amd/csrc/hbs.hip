@@ -2121,6 +2121,9 @@ static void level_launch(hipStream_t s, const LevelApply<R>& A, const cplx<R>* i
   LSH_LAUNCH_CHECK();
 }
 
+// (2^27 entries of 16 bytes are 2^31; a block that fits level_fits is far below the other 2^31)
+bool level_offsets_fit(long between) { return between >= 0 && between <= (1L << 27); }
+
 template <typename R>
 bool level_fits(int c, int k, int r, bool transposed) {
   const int n = transposed ? std::max(level_lds(2, c, k, r), level_lds(3, c, k, r))

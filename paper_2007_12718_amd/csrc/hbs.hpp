@@ -126,6 +126,9 @@ constexpr size_t LEVEL_FUSED_LDS = 64 * 1024;
 // whether one box vector fits it
 template <typename R>
 bool level_fits(int c, int k, int r, bool transposed);
+// whether G_ba, `between` entries behind G_ab, can be reached from it: the
+// kernels add unsigned 32-bit byte offsets to G_ab's address
+bool level_offsets_fit(long between);
 // out[v] (k) = U^T X_tau in[v] (in: [nvec][2c])
 template <typename R>
 void level_up_fused(hipStream_t s, const LevelApply<R>& A, const cplx<R>* in, cplx<R>* out, int nvec);

@@ -1653,8 +1653,7 @@ bool level_fused(const lsh_plan_s& P, FactorData<R>& F, int l, int B, LevelApply
   if (g_apply_fused_min == 0 || l < 1 || l >= P.L || P.lev[l].ident || F.wr[l] <= 0) return false;
   const int c = P.lev[l].c, k = P.lev[l].k, r = F.wr[l];
   if (!level_fits<R>(c, k, r, transposed)) return false;
-  // (the kernels reach both sibling blocks from the first with 32-bit offsets)
-  if (std::llabs((long long)(P.Gabt<R>(l) - P.Gab<R>(l))) > (1LL << 27)) return false;
+  if (!level_offsets_fit(P.Gabt<R>(l) - P.Gab<R>(l))) return false;
   if (g_apply_fused_min > 0 ? B < g_apply_fused_min
                             : c > kApplyFusedSmall && (c > kApplyFusedMost || B < kApplyFusedMin))
     return false;
