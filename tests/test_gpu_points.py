@@ -172,3 +172,33 @@ def test_groups_of_fields_on_the_grid(n, leaf, npts, nrhs):
     for r in range(nrhs):
         assert np.abs(out[r] - ref[r]).max() <= tol * np.abs(ref).max(), r
         assert np.abs(back[r] - refb[r]).max() <= tol * np.abs(refb).max(), r
+
+
+@pytest.mark.parametrize("n,leaf,npts,nrhs", [(96, 6, 1, 1), (96, 6, 7, 2), (96, 6, 5, 4), (96, 6, 9, 8), (64, 8, 3, 17)])
+def test_captured_calls(n, leaf, npts, nrhs):
+    """Under capture the forward sums take the grid in one part, without the plan's memory: replays on new inputs,
+    with eager calls between them, against the eager results."""
+    import torch
+    from paper_2007_12718_amd import lsh
+    P = lsh.Plan(n, 0.5 * n, op_order=4, leaf=leaf, tol=1e-2, proxy_width=1, prec="fp64")
+    gen = torch.Generator(device="cuda").manual_seed(npts)
+
+    def field(*shape):
+        return torch.randn(*shape, dtype=torch.complex128, device="cuda", generator=gen)
+
+    xy = 0.6 + torch.rand(npts, 2, dtype=torch.float64, device="cuda", generator=gen)
+    sig, g = field(nrhs, n, n), field(nrhs, npts)
+    P.eval_points(sig, xy)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out, back = P.eval_points(sig, xy), P.eval_points_adjoint(g, xy)
+    for _ in range(3):
+        sig.copy_(field(nrhs, n, n))
+        g.copy_(field(nrhs, npts))
+        graph.replay()
+        ref, refb = P.eval_points(sig, xy), P.eval_points_adjoint(g, xy)
+        torch.cuda.synchronize()
+        # (another order of the sum over the nodes)
+        assert float((out - ref).abs().max()) <= 1e-13 * float(ref.abs().max()) * max(1.0, n ** 0.5 / 8)
+        assert torch.equal(back, refb)
