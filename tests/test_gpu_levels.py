@@ -46,3 +46,30 @@ def test_fused_levels_match_batched_products(n, leaf, kh, prec, tol):
                     assert float((one[0] - ref[nrhs - 1]).abs().max() / ref.abs().max()) <= tol
     finally:
         lsh.apply_fused_levels(-1)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("n,leaf,kh", [(16, 4, 0.5), (40, 5, 0.6), (64, 8, 0.3), (112, 7, 0.5), (192, 6, 0.62)])
+def test_the_comparison_above_runs_the_fused_kernels(n, leaf, kh, prec):
+    """Its thresholds launch what it compares: both one-launch passes of either direction, or none of them."""
+    import torch
+    from paper_2007_12718_amd import lsh
+    b = cuda(synth.bumps(n, np.random.default_rng(n)))
+    P = lsh.Plan(n, kh * n, op_order=4, leaf=leaf, tol=1e-4, proxy_width=2, prec=prec, merge="lowrank")
+    F = lsh.Factor(P, b, transpose=True)
+    x = torch.ones((3, n, n), dtype=torch.complex128, device="cuda")
+    F.apply_precond(x, transpose=True)  # (the first one builds the transposed copies)
+    names = [f"level_{p}_{'f32' if prec == 'fp32' else 'f64'}" for p in ("up", "down", "tup", "tdown")]
+    try:
+        for least in (1, -1, 0):
+            for tr in (False, True):
+                lsh.apply_fused_levels(least)
+                lsh.lsh_profile_enable(True)
+                F.apply_precond(x, transpose=tr)
+                ran = [lsh.lsh_profile_query(k)[0] > 0 for k in names]
+                lsh.lsh_profile_enable(False)
+                want = [not tr, not tr, tr, tr] if least else [False] * 4
+                assert ran == want, (least, tr, ran)
+    finally:
+        lsh.lsh_profile_enable(False)
+        lsh.apply_fused_levels(-1)
