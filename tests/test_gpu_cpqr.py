@@ -66,3 +66,21 @@ def test_plans_repeat_bit_for_bit():
         for (J, _, U), (Jr, _, Ur) in zip(got, ref):
             assert np.array_equal(J, Jr) and torch.equal(U, Ur)
         P.close()
+
+
+def test_the_grids_above_reach_every_template():
+    """Ranks for each interpolation kernel and row lengths for each step kernel, among two of the grids above."""
+    from paper_2007_12718_amd import lsh
+    ranks, cols = set(), set()
+    for n, leaf, order, tol, width, kh in [(48, 6, 6, 1e-9, 2, 0.6), (128, 8, 10, 1e-12, 3, 1.2)]:
+        P = lsh.Plan(n, kh * n, op_order=order, leaf=leaf, tol=tol, proxy_width=width, prec="fp64", hbs_order=order,
+                     merge="schur")
+        L, r = P.ranks()
+        ranks |= set(r[1:])
+        for l in range(1, L + 1):
+            sx, sy = hbs.Compression(n, kh * n, leaf, 0.5, width, order=order).tree.box(l, 0)[2:]
+            cols.add(2 * len(hbs.proxy_ring(sx, sy, width)))
+    for lo, hi in [(0, 64), (64, 128), (128, 256), (256, 512), (512, 1 << 30)]:
+        assert any(lo < k <= hi for k in ranks), (lo, hi, ranks)
+    # (a step of column j sees the rows from j on: the longest row passes every shorter class as j advances)
+    assert max(cols) > 2048, cols
