@@ -2854,18 +2854,23 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
   int running = 3;                   // plan threads still running
   bool finished = false, failed = false;
   std::exception_ptr err;
+  // the first failure, of the plan or the factor, is the build's: what it stops
+  // elsewhere may throw as well
   auto fail = [&] {
-    std::lock_guard<std::mutex> g(mu);
-    if (!err) err = std::current_exception();
-    failed = true;
+    {
+      std::lock_guard<std::mutex> g(mu);
+      if (!failed) err = std::current_exception();
+      failed = true;
+    }
+    cv.notify_all();
   };
   auto leave = [&] {
     { std::lock_guard<std::mutex> g(mu); finished = --running == 0; }
     cv.notify_all();
   };
-  // two plan threads: the row IDs of levels L..1 (the critical path), and
-  // behind them the sibling blocks of parent levels L-1..0 with their
-  // low-rank forms (sibling block l needs the skeletons of level l + 1).
+  // plan threads: the row IDs of levels L..1 (the critical path), their
+  // interpolation matrices (below), and the sibling blocks of parent levels
+  // L-1..0 with their low-rank forms (sibling block l needs the skeletons of level l + 1).
   // Sibling levels are claimed in order by either thread: once its row IDs
   // are done, the first thread takes the next unclaimed one (the last two,
   // typically: they need the same skeletons and run side by side).
@@ -3025,7 +3030,6 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
       }
     } catch (...) {
       fail();
-      cv.notify_all();
     }
     leave();
   });
@@ -3035,7 +3039,6 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
     cv.wait(g, [&] { return failed || finished || (kind ? sibDone[l] != 0 : doneU <= l); });
     return !failed;
   };
-  std::exception_ptr ferr;
   try {
     auto run = [&](auto& FD) {
       factor_init(*P, FD);
@@ -3071,18 +3074,13 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
     };
     if (desc->hbs_prec == LSH_FP32) run(F->f32);
     else run(F->f64);
-  } catch (...) {
-    ferr = std::current_exception();
-  }
-  if (ferr) {  // let the plan threads stop early
-    { std::lock_guard<std::mutex> g(mu); failed = true; }
-    cv.notify_all();
+  } catch (...) {  // (the plan threads stop early)
+    fail();
   }
   th.join();
   th2.join();
   th3.join();
   if (err) std::rethrow_exception(err);
-  if (ferr) std::rethrow_exception(ferr);
   LSH_HIP(hipStreamWaitEvent(s, ev[2 * L + 2], 0));
   LSH_HIP(hipStreamSynchronize(s));
   *plan = P.release();
