@@ -2943,7 +2943,7 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
   if (defer) P->interp_wait = wait_interp;
   const char* ess = std::getenv("LSH_SIB_SYNC");
   const bool sib_sync = !(ess && *ess == '0');
-  std::thread th([&] {
+  auto row_ids = [&] {
     try {
       LSH_HIP(hipSetDevice(dev));
       mem::Bind tbind(&P->persist);
@@ -2992,8 +2992,8 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
       fail();
     }
     leave();
-  });
-  std::thread th2([&] {
+  };
+  auto siblings = [&] {
     try {
       LSH_HIP(hipSetDevice(dev));
       mem::Bind tbind(&P->persist);
@@ -3003,8 +3003,8 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
       fail();
     }
     leave();
-  });
-  std::thread th3([&] {
+  };
+  auto interpolations = [&] {
     try {
       LSH_HIP(hipSetDevice(dev));
       mem::Bind tbind(&P->persist);
@@ -3032,7 +3032,15 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
       fail();
     }
     leave();
-  });
+  };
+  std::thread th[3];
+  try {
+    th[0] = std::thread(row_ids);
+    th[1] = std::thread(siblings);
+    th[2] = std::thread(interpolations);
+  } catch (...) {  // (no thread to be had: those that run stop, and the call fails)
+    fail();
+  }
   // wait until U_l (kind 0) or G_l (kind 1) exists; false if the plan failed
   auto wait_for = [&](int l, int kind) -> bool {
     std::unique_lock<std::mutex> g(mu);
@@ -3077,9 +3085,8 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
   } catch (...) {  // (the plan threads stop early)
     fail();
   }
-  th.join();
-  th2.join();
-  th3.join();
+  for (std::thread& t : th)
+    if (t.joinable()) t.join();
   if (err) std::rethrow_exception(err);
   LSH_HIP(hipStreamWaitEvent(s, ev[2 * L + 2], 0));
   LSH_HIP(hipStreamSynchronize(s));

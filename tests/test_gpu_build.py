@@ -92,3 +92,48 @@ def test_a_level_just_below_its_bound():
     P2, F2 = lsh.build(n, 0.6 * n, b, **o)
     assert P2.ranks() == P.ranks()
     assert torch.equal(F2.apply_precond(x), y)
+
+
+STARVED = r"""
+import resource, sys, threading
+import numpy as np
+import torch
+import synth
+from paper_2007_12718_amd import lsh
+
+b = torch.from_numpy(synth.bumps(64, np.random.default_rng(0))).cuda()
+o = dict(op_order=4, leaf=8, tol=1e-4, proxy_width=2, prec="fp32")
+P, F = lsh.build(64, 30.0, b, **o)
+x = torch.ones((1, 64, 64), dtype=torch.complex128, device="cuda")
+y = F.apply_precond(x)
+torch.cuda.synchronize()
+soft, hard = resource.getrlimit(resource.RLIMIT_NPROC)
+resource.setrlimit(resource.RLIMIT_NPROC, (0, hard))
+try:
+    threading.Thread(target=int).start()
+    print("THREADS ARE NOT LIMITED HERE", flush=True)
+    sys.exit(0)
+except RuntimeError:
+    pass
+try:
+    lsh.build(64, 30.0, b, **o)
+    print("BUILT", flush=True)
+except lsh.LshError as e:
+    print("REPORTED", e.code, flush=True)
+resource.setrlimit(resource.RLIMIT_NPROC, (soft, hard))
+P2, F2 = lsh.build(64, 30.0, b, **o)
+assert torch.equal(F2.apply_precond(x), y)
+print("BUILT AFTERWARDS", flush=True)
+"""
+
+
+def test_a_build_without_threads_is_an_error():
+    """A process that may start no thread gets an error code from lsh_build, and builds again once it may."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", STARVED], cwd=root, capture_output=True, text=True, timeout=100)
+    if "NOT LIMITED" in r.stdout:
+        pytest.skip("this user's threads are not limited")
+    assert r.returncode == 0 and "REPORTED -4" in r.stdout and "BUILT AFTERWARDS" in r.stdout, (r.stdout, r.stderr)
