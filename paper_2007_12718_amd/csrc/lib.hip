@@ -3087,7 +3087,10 @@ int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, s
   }
   for (std::thread& t : th)
     if (t.joinable()) t.join();
-  if (err) std::rethrow_exception(err);
+  if (err) {  // (queued work still uses the workspaces, which the caller may free now)
+    for (hipStream_t q : {ps, ps2, fs}) (void)hipStreamSynchronize(q);
+    std::rethrow_exception(err);
+  }
   LSH_HIP(hipStreamWaitEvent(s, ev[2 * L + 2], 0));
   LSH_HIP(hipStreamSynchronize(s));
   *plan = P.release();
