@@ -534,14 +534,17 @@ static const TileModel kF32Model[2] = {{1, 128, 64, 2, 1.00}, {0, 64, 64, 3, 0.9
 
 // FP64, by the number of 64 x 64 output tiles t64 and 32 x 32 ones t32: the
 // small tile, four workgroups to a compute unit, where the large one gives
-// fewer than its two to each (a product alone takes 13 us with 64 x 64 tiles and 6 with 32 x 32 at
-// order 64, 80 and 29 at 512, 335 and 312 at 1000 x 1000 x 2000), and past that
-// where its rounds come out shorter (1600^3, 625 tiles: 636 and 530 us; 2000 x
-// 1000 x 1000, 512 tiles: 288 and 290).  The 32-deep stages: 68 TF/s at 4096^3
-// with either depth, 51 against 48 at 1280^3; 61 and 37 with 128 x 64 tiles.
+// fewer than its two to each (a product alone takes 13 us with 64 x 64 tiles
+// and 6 with 32 x 32 at order 64, 80 and 29 at 512, 335 and 312 at 1000 x 1000
+// x 2000), and past that where its rounds come out shorter by more than the
+// large tile is faster in full ones: with the small tile's rounds against two
+// of the large one's at 0.75 (1600^2 x 800) 303 us against 346, at 0.9
+// (2900^2 x 800) 901 and 939, at 0.94 (4160^2 x 500) 1177 and 1136, at 0.97
+// (6000^2 x 300) 1566 and 1491.  The 32-deep stages: 68 TF/s at 4096^3 with
+// either depth, 51 against 48 at 1280^3; 61 and 37 with 128 x 64 tiles.
 static int f64_variant(long t64, long t32) {
   const long r64 = (t64 + 511) / 512, r32 = (t32 + 1023) / 1024;
-  return t64 < 512 || r32 < 2 * r64 ? 3 : 2;
+  return t64 < 512 || 25 * r32 < 46 * r64 ? 3 : 2;
 }
 
 static int model_variant(int prec, int M, int N, int batch) {

@@ -72,3 +72,25 @@ def test_an_infinity_stays_in_its_row(prec):
     C = _product(A.cuda(), B.cuda()).cpu()[0]
     assert not torch.isfinite(torch.view_as_real(C[0])).all()
     assert (C[1:] == 37).all()
+
+
+@pytest.mark.parametrize("order,name", [(64, "cgemm_f64_32x32k32"), (1600, "cgemm_f64_32x32k32"),
+                                        (2048, "cgemm_f64_64x64k32"), (4160, "cgemm_f64_64x64k32"),
+                                        (6000, "cgemm_f64_64x64k32")])
+def test_fp64_tile_by_rounds(order, name):
+    """Without a table: the small tile for one round or clearly shorter ones, the large one for many full rounds."""
+    import torch
+    from paper_2007_12718_amd import lsh
+    A = torch.randn(1, order, 8, dtype=torch.complex128, device="cuda")
+    B = torch.randn(1, 8, order, dtype=torch.complex128, device="cuda")
+    lsh.gemm_table_clear()
+    try:
+        lsh.lsh_profile_enable(True)
+        C = lsh.dev_gemm(A, B)
+        names = lsh.lsh_profile_names()
+    finally:
+        lsh.lsh_profile_enable(False)
+        lsh.gemm_table_load(lsh.GEMM_TABLE)
+    assert [k for k in names if k.startswith("cgemm")] == [name]
+    # sums of eight products of normal numbers: below 8 * 16 * 2^-53 times the largest
+    assert float((C - A @ B).abs().max()) <= 1e-13
