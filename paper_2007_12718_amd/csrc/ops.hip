@@ -2,6 +2,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "../../include/lsh.h"
 #include "ops.hpp"
 #include "prof.hpp"
 #include "wave.hpp"
@@ -127,14 +128,14 @@ void multidot(hipStream_t s, const z64* V, long ldv, int nv, const z64* w, long 
 // 320 us, and the solve of 8 fields on 512 x 512 14.8 ms against 13.9.  (The
 // workgroups go to running vectors only: 30 unpreconditioned iterations for
 // one of eight on 1024 x 1024 take 26.4 ms, 46.7 with an eighth for each.)
-constexpr int CGS_NT = 1024, CGS_E = 4, CGS_WG = 256;
+constexpr int CGS_NT = 1024, CGS_E = 4, CGS_WG = 256, CGS_MAXV = LSH_MAX_ITERS;
 
 template <int STEP>
 __global__ __launch_bounds__(CGS_NT) void k_cgs(const z64* __restrict__ V, long ldv, int nv, z64* w, long N,
                                                 unsigned active, const z64* __restrict__ pin, z64* __restrict__ pout,
                                                 z64* h, int hs) {
-  __shared__ z64 red[STEP <= 1 ? MD_MAXV : 1][CGS_NT / 64];
-  __shared__ z64 hv[STEP == 0 ? 1 : MD_MAXV];
+  __shared__ z64 red[STEP <= 1 ? CGS_MAXV : 1][CGS_NT / 64];
+  __shared__ z64 hv[STEP == 0 ? 1 : CGS_MAXV];
   const int q = blockIdx.y, nb = gridDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int k = 0; k < q; ++k) active &= active - 1;
   const int r = __builtin_ctz(active);  // the q-th running vector
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(CGS_NT) void k_cgs(const z64* __restrict__ V, long 
 void cgs2(hipStream_t s, const z64* V, long ldv, int nv, z64* w, long N, int nr, unsigned active, z64* h1, z64* h2,
           int hs, z64* partial) {
   ProfScope ps("gram_schmidt", s, 16.0 * (double)N * (3 * nv + 7) * __builtin_popcount(active));
-  LSH_REQUIRE(nv <= MD_MAXV && nr >= 1 && nr <= 32, -6, "gram-schmidt: too many vectors");
+  LSH_REQUIRE(nv <= CGS_MAXV && nr >= 1 && nr <= 32, -6, "gram-schmidt: too many vectors");
   const int na = __builtin_popcount(active);
   if (na == 0) return;
   // the running vectors share the workgroups; every workgroup has a piece of

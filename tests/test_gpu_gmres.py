@@ -85,3 +85,26 @@ def test_vectors_left_in_a_group_solve_what_single_runs_solve(n, running):
         assert (sig.reshape(8, n, n)[r] - one).norm() <= 2e-11 * 10 * max(one.norm().item(), 1e-300)
     F.close()
     P.close()
+
+
+@pytest.mark.parametrize("nrhs", [1, 3])
+def test_every_iteration_that_the_interface_admits(nrhs):
+    """200 iterations (LSH_MAX_ITERS) without a restart, on a problem that needs more."""
+    n, kappa = 24, 60.0
+    rng = np.random.default_rng(0)
+    b = torch.from_numpy(rng.uniform(0.2, 1.0, (n, n))).cuda()
+    P, F = lsh.build(n, kappa, b, op_order=4, leaf=12, tol=1e-8, prec="fp64")
+    u = torch.from_numpy(rng.standard_normal((nrhs, n, n)) + 1j * rng.standard_normal((nrhs, n, n))).cuda()
+    eye = torch.eye(n * n, dtype=torch.complex128, device="cuda").reshape(n * n, n, n)
+    A = P.apply_operator(b, eye).reshape(n * n, n * n).T.cpu().numpy()
+    f = (-kappa ** 2 * b * u)[-1].reshape(-1).cpu().numpy()
+    sig, _, info, rc = F.solve(u, tol=1e-13, maxit=200, precondition=False, want_u=False)
+    assert rc == 1 and info.iterations == 200
+    hist = np.array(info.history[:201])
+    ref = _gmres_history(A, f, 200)
+    tol = 100 * len(hist) * np.linalg.cond(A) * 2.0 ** -53  # (as above)
+    assert np.abs(hist - ref).max() <= tol, (np.abs(hist - ref).max(), tol)
+    last = sig.reshape(nrhs, -1)[-1].cpu().numpy()
+    assert abs(np.linalg.norm(f - A @ last) / np.linalg.norm(f) - ref[-1]) <= tol
+    F.close()
+    P.close()
