@@ -343,7 +343,7 @@ size_t rowid_cpqr_ws(int m) {
   return (size_t)m * (2 * sizeof(double) + sizeof(z64) + sizeof(int)) + sizeof(CpqrState) + 5 * 256;
 }
 
-int rowid_cpqr(hipStream_t s, z64* A, int m, int np, double tol, int* J, z64* U, void* ws,
+int rowid_cpqr(hipStream_t s, z64* A, int m, int np, double tol, int* J, std::vector<int>& Jh, z64* U, void* ws,
                const std::function<void(int)>& on_skel) {
   ProfScope ps("cpqr", s, 16.0 * (double)m * np);
   char* wp = static_cast<char*>(ws);
@@ -389,15 +389,17 @@ int rowid_cpqr(hipStream_t s, z64* A, int m, int np, double tol, int* J, z64* U,
     fill_zero(s, U, sizeof(z64) * (size_t)m);
     LSH_HIP(hipMemcpyAsync(U, &one, sizeof(z64), hipMemcpyHostToDevice, s));
     LSH_HIP(hipStreamSynchronize(s));
+    Jh.assign(1, 0);
     if (on_skel) on_skel(k);
     return k;
   }
   // the skeleton to the host: the other rows' list, and the caller's notice
-  std::vector<int> ph(k), rh;
-  LSH_HIP(hipMemcpyAsync(ph.data(), J, sizeof(int) * k, hipMemcpyDeviceToHost, s));
+  std::vector<int> rh;
+  Jh.resize(k);
+  LSH_HIP(hipMemcpyAsync(Jh.data(), J, sizeof(int) * k, hipMemcpyDeviceToHost, s));
   LSH_HIP(hipStreamSynchronize(s));
   std::vector<char> used(m, 0);
-  for (int v : ph) {
+  for (int v : Jh) {
     LSH_REQUIRE(v >= 0 && v < m && !used[v], -4, "row ID: skeleton rows not distinct");
     used[v] = 1;
   }

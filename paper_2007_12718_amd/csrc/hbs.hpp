@@ -17,9 +17,10 @@ void gather_table(hipStream_t s, const z64* T, int D, const I2* rows, int m, con
 // Row interpolative decomposition A ~= U A[J, :] (U[J, :] = I) of the m x np
 // FP64 matrix A (destroyed).  CPQR path: Householder QR with column pivoting
 // of A^T, one launch per pivot; stops at the first |R_kk| <= tol ||A||_F.
-// Outputs: J (m ints, first k used), U (m x k, row-major).  Returns the rank
-// (synchronises on the stream once per batch of steps); on_skel as rowid_bp.
-int rowid_cpqr(hipStream_t s, z64* A, int m, int np, double tol, int* J, z64* U, void* ws,
+// Outputs: J (m ints, first k used; its host copy in Jh), U (m x k, row-major).
+// Returns the rank (synchronises on the stream once per batch of steps);
+// on_skel as rowid_bp, with Jh already there.
+int rowid_cpqr(hipStream_t s, z64* A, int m, int np, double tol, int* J, std::vector<int>& Jh, z64* U, void* ws,
                const std::function<void(int)>& on_skel = {});
 size_t rowid_cpqr_ws(int m);
 

@@ -332,7 +332,10 @@ int row_id_matrix(lsh_plan_s& P, z64* A, int m, int np, std::vector<int>& Jh, De
   // Gram + pivoted Cholesky squares the conditioning: FP64 resolves the
   // stopping rule only while tol stays above ~1e-7; below that, CPQR.
   if (P.d.tol < 1e-7) {
-    k = rowid_cpqr(s, A, m, np, P.d.tol, J, Ufull, scr.take(rowid_cpqr_ws(m)), skel);
+    k = rowid_cpqr(s, A, m, np, P.d.tol, J, Jh, Ufull, scr.take(rowid_cpqr_ws(m)), [&](int kk) {
+      told = true;  // (Jh is there)
+      if (on_skel) on_skel(kk);
+    });
   } else {
     // block-pivoted left-looking Cholesky by default (alpha-greedy with
     // alpha = LSH_BP_ALPHA, default 0.65; 1 = greedy); LSH_ROWID=panel selects
