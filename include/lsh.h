@@ -229,7 +229,8 @@ int lsh_factor_workspace_used(lsh_factor_t factor, size_t* used, size_t* size);
  * plan_bytes as lsh_plan_workspace, factor_bytes at least what
  * lsh_factor_workspace would give once the plan exists).  The interpolation
  * matrix of a level is formed beside the next level's row ID where plan_ws has
- * room for both levels' temporaries (it does at the ranks met in practice).
+ * room for both levels' temporaries (as a rule; with proxy_width 1 the top
+ * levels' ranks come close to their bounds, and there they take turns).
  * Errors: as lsh_plan_create and lsh_factor_create. */
 int lsh_build_workspace(const lsh_desc* desc, int flags, size_t* plan_bytes, size_t* factor_bytes);
 int lsh_build(const lsh_desc* desc, const double* b, int flags, void* plan_ws, size_t plan_ws_bytes,

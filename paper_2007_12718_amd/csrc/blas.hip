@@ -813,8 +813,9 @@ template void mirror_lower<float>(hipStream_t, cplx<float>*, int, long);
 // k = 16 c + 4 (l / 16) of row (or vector) l % 16, which fills whole lines, and
 // the instruction does not care which four k of a chunk its lane groups hold.
 // A workgroup takes 16 rows of one matrix and 16 NT vectors; its KS wavefronts
-// take the 16-deep chunks in turn and their sums meet in LDS in order.  A
-// vector's sums do not depend on how many others there are.  Bound by the bytes
+// take the 16-deep chunks in turn and their sums meet in LDS in order
+// (fixed for a product's sizes; KS, and the order with it, changes with the
+// number of vectors).  Bound by the bytes
 // of A (or, at the top levels, by a wavefront's chain of chunks).  With a
 // wavefront per row and the vectors' products on the vector unit every row
 // read all the vectors again, and eight vectors of a matrix took two launches:

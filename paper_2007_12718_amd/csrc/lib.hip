@@ -111,15 +111,16 @@ struct lsh_plan_s {
   const z64* hbs_table() const { return htable.p ? htable.as<z64>() : table.as<z64>(); }
   // Device memory, all from the caller's plan workspace: persist holds what
   // the plan keeps; sid and ssib hold the temporaries of the level row IDs
-  // and of the sibling blocks (the two plan threads of lsh_build), each
-  // rewound at the start of its next level, after a stream synchronisation;
-  // sgram holds the parent level's Gram rows built during a level's row ID
-  // (rewound once they are packed into the parent's row-ID workspace).
+  // and of the sibling blocks, each rewound at the start of its next level,
+  // after a stream synchronisation (in lsh_build sid is split, below); sgram
+  // holds the parent level's Gram rows built during a level's row ID (rewound
+  // once they are packed into the parent's row-ID workspace).
   mem::Arena persist, sid, ssib, sgram;
   // In lsh_build a level's interpolation matrix is formed beside the next
   // level's row ID (interp_wait is set), so two levels' temporaries share sid:
   // alternate levels lie at its two ends, sized by the actual candidates (sid
-  // is sized by bounds of about twice those, so four times the bytes).
+  // is sized by a bound on them; commonly they are half of it, so a quarter of
+  // the bytes; near the bound, with one layer of proxies, levels take turns).
   // interp_wait(l) returns once level l's are free; false: the build failed.
   std::function<bool(int)> interp_wait;
   mem::Arena id_end[2];
@@ -465,7 +466,7 @@ void level_id(lsh_plan_s& P, int l, Level& lv, const std::vector<I2>& prox, hipS
     if (P.hbs_order > 4) gather_table(s, P.hbs_table(), P.D, dc, m, dp, np, A + np, ncols);
   }
   auto gram = [&](z64* M, bool& ready) -> NextGram* {
-    if (pre) {  // (the side stream was synchronised at the start of this level)
+    if (pre) {  // (plan_id put s behind the side stream's rows: a synchronisation, in lsh_build their event)
       next_gram_pack(s, P.ng, m / 2, M);
       ready = true;
     }
