@@ -563,8 +563,8 @@ __global__ void k_gather_rows(const z64* Lt, int m, const int* rest, int nr, int
 // 16 x 16 diagonal blocks by forward substitution, a thread per column with
 // the column in registers, then joined by doubling (inv [[A, 0], [B, C]] =
 // [[A^-1, 0], [-C^-1 B A^-1, C^-1]]).  Bound by its chain of LDS latencies:
-// 16 dependent steps and four barriers, 32 us a launch; 64 steps with a lane
-// exchange each took 130.
+// 16 dependent steps and four barriers, 32 us a launch at n = 256; 64 steps
+// with a lane exchange each took 130.
 constexpr int TRI_B = 64;
 __global__ __launch_bounds__(256) void k_trinv_blocks(const z64* L11, int k, z64* Dinv) {
   constexpr int S = 16, LD = TRI_B + 1;
