@@ -528,7 +528,11 @@ const char* gemm_variant_name(int prec, int v) {
 // round costs (resident workgroups x tile area) / (per-CU efficiency of that
 // tile)), from rates of 168 TF/s for the 128 x 64 tile and 160 for 64 x 64 at
 // 4096^3, 120 against 97 for 256 products of order 128, 50 against 85 for 1024
-// of order 64.  For FP64 see f64_variant.
+// of order 64.  Whole rounds flatter the larger tile where its edge is mostly
+// padding, and its rate comes with depth, so it is taken only where it covers
+// no more area (32 products of 300 x 1000 x 512: 372 us with it, 308 with 64 x
+// 64) and K goes beyond one stage (1024 of 76 x 1243 x 10: 492 and 450).  For
+// FP64 see f64_variant.
 struct TileModel { int variant, bm, bn, resident; double eff; };
 static const TileModel kF32Model[2] = {{1, 128, 64, 2, 1.00}, {0, 64, 64, 3, 0.95}};
 
@@ -547,9 +551,10 @@ static int f64_variant(long t64, long t32) {
   return t64 < 512 || 25 * r32 < 46 * r64 ? 3 : 2;
 }
 
-static int model_variant(int prec, int M, int N, int batch) {
+static int model_variant(int prec, int M, int N, int K, int batch) {
   if (prec != 1)
     return f64_variant((long)ceil_div(M, 64) * ceil_div(N, 64) * batch, (long)ceil_div(M, 32) * ceil_div(N, 32) * batch);
+  if (K <= 32 || ceil_div(M, 128) * 2 > ceil_div(M, 64)) return 0;
   int best = 0;
   double bt = 1e300;
   for (const TileModel& tm : kF32Model) {
@@ -596,7 +601,7 @@ static int choose_variant(int prec, int M, int N, int K, int batch) {
     auto it = g_tune.find(tune_key(prec, M, N, K, batch));
     if (it != g_tune.end() && it->second < nv) return it->second;
   }
-  return model_variant(prec, M, N, batch);
+  return model_variant(prec, M, N, K, batch);
 }
 
 void gemm_force_variant(int v) { g_forced_variant = v; }

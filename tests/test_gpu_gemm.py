@@ -94,3 +94,25 @@ def test_fp64_tile_by_rounds(order, name):
     assert [k for k in names if k.startswith("cgemm")] == [name]
     # sums of eight products of normal numbers: below 8 * 16 * 2^-53 times the largest
     assert float((C - A @ B).abs().max()) <= 1e-13
+
+
+@pytest.mark.parametrize("M,N,K,batch,name", [(256, 256, 128, 64, "cgemm_f32_128x64"), (300, 1000, 64, 32, "cgemm_f32_64x64"),
+                                              (76, 1243, 10, 64, "cgemm_f32_64x64"), (64, 64, 64, 8, "cgemm_f32_64x64")])
+def test_fp32_tile_by_area_and_depth(M, N, K, batch, name):
+    """Without a table: the larger tile only beyond one K stage and where its edge covers no more than 64 x 64 tiles."""
+    import torch
+    from paper_2007_12718_amd import lsh
+    A = torch.randn(batch, M, K, dtype=torch.complex64, device="cuda")
+    B = torch.randn(batch, K, N, dtype=torch.complex64, device="cuda")
+    lsh.gemm_table_clear()
+    try:
+        lsh.lsh_profile_enable(True)
+        C = lsh.dev_gemm(A, B)
+        names = lsh.lsh_profile_names()
+    finally:
+        lsh.lsh_profile_enable(False)
+        lsh.gemm_table_load(lsh.GEMM_TABLE)
+    assert [k for k in names if k.startswith("cgemm")] == [name]
+    ref = (A[0].to(torch.complex128) @ B[0].to(torch.complex128)).abs().max()
+    # 3 K + 4 roundings of a sum of K products, three real products to a complex one
+    assert float((C[0] - A[0].to(torch.complex128) @ B[0].to(torch.complex128)).abs().max()) <= (3 * K + 4) * 2.0 ** -24 * float(ref)
