@@ -96,8 +96,9 @@ def test_fp64_tile_by_rounds(order, name):
     assert float((C - A @ B).abs().max()) <= 1e-13
 
 
-@pytest.mark.parametrize("M,N,K,batch,name", [(256, 256, 128, 64, "cgemm_f32_128x64"), (300, 1000, 64, 32, "cgemm_f32_64x64"),
-                                              (76, 1243, 10, 64, "cgemm_f32_64x64"), (64, 64, 64, 8, "cgemm_f32_64x64")])
+@pytest.mark.parametrize("M,N,K,batch,name", [
+    (256, 256, 128, 64, "cgemm_f32_128x64"), (300, 1000, 64, 32, "cgemm_f32_64x64"),
+    (76, 1243, 10, 64, "cgemm_f32_64x64"), (64, 64, 64, 8, "cgemm_f32_64x64")])
 def test_fp32_tile_by_area_and_depth(M, N, K, batch, name):
     """Without a table: the larger tile only beyond one K stage and where its edge covers no more than 64 x 64 tiles."""
     import torch
@@ -113,6 +114,6 @@ def test_fp32_tile_by_area_and_depth(M, N, K, batch, name):
         lsh.lsh_profile_enable(False)
         lsh.gemm_table_load(lsh.GEMM_TABLE)
     assert [k for k in names if k.startswith("cgemm")] == [name]
-    ref = (A[0].to(torch.complex128) @ B[0].to(torch.complex128)).abs().max()
+    ref = A[0].to(torch.complex128) @ B[0].to(torch.complex128)
     # 3 K + 4 roundings of a sum of K products, three real products to a complex one
-    assert float((C[0] - A[0].to(torch.complex128) @ B[0].to(torch.complex128)).abs().max()) <= (3 * K + 4) * 2.0 ** -24 * float(ref)
+    assert float((C[0] - ref).abs().max()) <= (3 * K + 4) * 2.0 ** -24 * float(ref.abs().max())

@@ -174,7 +174,8 @@ def test_groups_of_fields_on_the_grid(n, leaf, npts, nrhs):
         assert np.abs(back[r] - refb[r]).max() <= tol * np.abs(refb).max(), r
 
 
-@pytest.mark.parametrize("n,leaf,npts,nrhs", [(96, 6, 1, 1), (96, 6, 7, 2), (96, 6, 5, 4), (96, 6, 9, 8), (64, 8, 3, 17)])
+@pytest.mark.parametrize("n,leaf,npts,nrhs", [(96, 6, 1, 1), (96, 6, 7, 2), (96, 6, 5, 4), (96, 6, 9, 8),
+                                               (64, 8, 3, 17)])
 def test_captured_calls(n, leaf, npts, nrhs):
     """Under capture the forward sums take the grid in one part, without the plan's memory: replays on new inputs,
     with eager calls between them, against the eager results."""
